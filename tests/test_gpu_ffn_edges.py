@@ -1,0 +1,118 @@
+"""The expert MLP's grouped GEMMs at the edges of their tiles (GPU).
+
+Row counts around the 32-row matrix-core blocks, the waves' 64- and 128-row
+shares and the 256-row tiles, widths that end inside a 64-deep stage and inside
+a tile's columns, experts without rows. Every product is compared on its own
+with a float64 product of the same bf16 operands (the backward's and the
+down-projection's operands are the GPU's own earlier outputs), and rows past an
+expert's count hold NaN on input and must stay as they were on output.
+
+Bound per element: an f32 sum of K exact products lies within
+gamma_K sum |a b| of the exact one (gamma_K ~ K 2^-24; K + 8 here for the bias
+and partial sums), a bf16 result is rounded once more (2^-9, and 2^-8 is
+allowed). gelu and gelu' of a value off by b are off by at most 1.13 b and
+0.8 b (the largest |gelu'| and |gelu''|) and by their own error, 1e-6.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2608_16188_amd import vmoe as V
+
+from .gpu_common import say
+
+pytestmark = pytest.mark.gpu
+
+# (d, f, rows per expert)
+CASES = [
+    (72, 200, [1, 31, 32, 33, 0, 63, 64, 65]),
+    (128, 264, [127, 128, 129, 0, 96, 97]),
+    (192, 768, [255, 256, 257, 288, 289, 16]),
+    (320, 136, [511, 513, 40, 320, 321]),
+    (64, 64, [2, 191, 193]),
+    (520, 1032, [300, 5, 0, 449]),
+    (1024, 256, [33, 17, 290, 640]),
+]
+# 16 and more experts: dxe beside the weight gradients
+MANY = (200, 520, [0, 1, 7, 32, 33, 34, 63, 64, 65, 100, 127, 128, 129, 200, 255, 256, 257])
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    yield
+    torch.cuda.synchronize()
+
+
+def _gamma(k):
+    return (k + 8) * 2.0 ** -24
+
+
+def _check(name, got, ref, bound):
+    got = got.double().cpu()
+    bad = ~((got - ref).abs() <= bound)  # NaN counts as bad
+    assert not bad.any(), (name, int(bad.sum()), float((got - ref).abs().max()))
+
+
+def _bf16(ref, bound):
+    """Bound of a result that is rounded to bf16."""
+    return bound + 2.0 ** -8 * (ref.abs() + bound)
+
+
+@pytest.mark.parametrize("d,f,rows", CASES + [MANY], ids=lambda v: str(v) if isinstance(v, int) else "")
+def test_products_at_tile_edges(d, f, rows):
+    say("ffn edges", d, f, rows)
+    E, R = len(rows), max(rows)
+    s = V.make_shape(R * E, 1, d, f, E, 1, 1.0, V.VMOE_BF16, capacity_override=R)
+    assert V.vmoe_capacity(s) == R
+    gen = torch.Generator().manual_seed(d * 1000 + f)
+
+    def randn(*shape, scale=1.0):
+        return (torch.randn(*shape, generator=gen) * scale).to(torch.bfloat16)
+
+    def padded(t):
+        for e, n in enumerate(rows):
+            t[e, n:] = float("nan")
+        return t.cuda()
+
+    xe, dye = padded(randn(E, R, d)), padded(randn(E, R, d, scale=0.3))
+    w1, w2 = randn(E, f, d, scale=0.06).cuda(), randn(E, d, f, scale=0.06).cuda()
+    b1, b2 = randn(E, f, scale=0.1).cuda(), randn(E, d, scale=0.1).cuda()
+    counts = torch.tensor([rows], dtype=torch.int32).cuda()
+
+    def out(*shape, dtype=torch.bfloat16):
+        return torch.full(shape, 77.0, dtype=dtype, device="cuda")
+
+    act, act_grad, ye = out(E, R, f), out(E, R, f), out(E, R, d)
+    V.vmoe_expert_ffn_fwd(s, xe, counts, w1, b1, w2, b2, act, act_grad, ye)
+    dh, dxe = out(E, R, f), out(E, R, d)
+    g = {n: out(*sh, dtype=torch.float32) for n, sh in
+         dict(dw1=(E, f, d), db1=(E, f), dw2=(E, d, f), db2=(E, d)).items()}
+    V.vmoe_expert_ffn_bwd(s, xe, counts, w1, w2, act, act_grad, dye, dh, dxe, g["dw1"], g["db1"],
+                          g["dw2"], g["db2"])
+    torch.cuda.synchronize()
+
+    c = {n: t.double().cpu() for n, t in dict(xe=xe, dye=dye, w1=w1, w2=w2, b1=b1, b2=b2, act=act,
+                                              act_grad=act_grad, dh=dh).items()}
+    for e, n in enumerate(rows):
+        for name, t in dict(act=act, act_grad=act_grad, ye=ye, dh=dh, dxe=dxe).items():
+            assert (t[e, n:] == 77.0).all(), f"{name}[{e}]: rows past the expert's were written"
+        x, dy, a, ag, h = (c[k][e, :n] for k in ("xe", "dye", "act", "act_grad", "dh"))
+        W1, W2 = c["w1"][e], c["w2"][e]
+        H, Hb = x @ W1.T + c["b1"][e], _gamma(d) * (x.abs() @ W1.abs().T + c["b1"][e].abs())
+        cdf = 0.5 * (1 + torch.erf(H * np.sqrt(0.5)))
+        pdf = torch.exp(-0.5 * H * H) / np.sqrt(2 * np.pi)
+        _check("act", act[e, :n], H * cdf, _bf16(H * cdf, 1.13 * Hb + 1e-6))
+        _check("act_grad", act_grad[e, :n], cdf + H * pdf, _bf16(cdf + H * pdf, 0.8 * Hb + 1e-6))
+        Y = a @ W2.T + c["b2"][e]
+        _check("ye", ye[e, :n], Y, _bf16(Y, _gamma(f) * (a.abs() @ W2.abs().T + c["b2"][e].abs())))
+        D = (dy @ W2) * ag
+        _check("dh", dh[e, :n], D, _bf16(D, _gamma(d) * (dy.abs() @ W2.abs()) * ag.abs()))
+        X = h @ W1
+        _check("dxe", dxe[e, :n], X, _bf16(X, _gamma(f) * (h.abs() @ W1.abs())))
+        for name, p, q in (("dw1", h, x), ("dw2", dy, a)):
+            _check(name, g[name][e], p.T @ q, _gamma(n) * (p.abs().T @ q.abs()))
+        for name, p in (("db1", h), ("db2", dy)):
+            _check(name, g[name][e], p.sum(0), _gamma(n) * p.abs().sum(0))
