@@ -945,11 +945,15 @@ constexpr bool light_ok() {
 }
 
 // A light expert's tiles split into this many column parts (whole wave
-// columns each): one HBM stream per CU runs at a fraction of a CU's share of
-// the chip's bandwidth, so a light tile's weight panel is spread over CUs.
+// columns each, so the parts divide T's wave columns), of at most `slots`, the
+// expert's m-tile slots of the grid: one HBM stream per CU runs at a fraction
+// of a CU's share of the chip's bandwidth, so a light tile's weight panel is
+// spread over CUs.
 template <class T>
-constexpr int light_parts() {
-    return T::WGN % 4 == 0 ? 4 : (T::WGN % 2 == 0 ? 2 : 1);
+__device__ __forceinline__ int light_parts(int slots) {
+    if (T::WGN % 4 == 0 && slots >= 4) return 4;
+    if (T::WGN % 2 == 0 && slots >= 2) return 2;
+    return 1;
 }
 
 template <class T, class CFG, bool B_KMAJOR, int EPI, int GS>
@@ -1184,7 +1188,7 @@ void gemm_bf16_kernel(GemmBatch batch) {
     // (the d-wide row GEMMs: a few long tiles per expert; the f-wide ones have
     // many short light tiles already)
     const int lsplit = light_ok<T, A_KMAJOR, B_KMAJOR, EPI>() && (EPI == EPI_BIAS || EPI == EPI_STORE)
-                           ? min(light_parts<T>(), (batch.p[0].M + BM_ - 1) / BM_)
+                           ? light_parts<T>((batch.p[0].M + BM_ - 1) / BM_)
                            : 1;
     int qe = 0, qu = 0, qn = 0, qt = 0, qne = 0;  // quota: expert, rank, units, tiles, rows
     if constexpr (SCHED == 1) {

@@ -32,6 +32,11 @@ CASES = [
     (64, 64, [2, 191, 193]),
     (520, 1032, [300, 5, 0, 449]),
     (1024, 256, [33, 17, 290, 640]),
+    # a few rows in buffers of two, three and four m-tiles: column parts
+    (512, 128, [500, 20, 32]),
+    (512, 128, [600, 20, 1]),
+    (448, 128, [900, 9, 32]),
+    (192, 64, [700, 30]),
 ]
 # 16 and more experts: dxe beside the weight gradients
 MANY = (200, 520, [0, 1, 7, 32, 33, 34, 63, 64, 65, 100, 127, 128, 129, 200, 255, 256, 257])
