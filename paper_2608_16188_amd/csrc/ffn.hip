@@ -1,13 +1,15 @@
 // Expert MLP forward and backward as grouped GEMMs on gfx950.
 //
 // bf16 path: one templated matrix-core kernel, C[M x N] = sum_k A(m,k) B(n,k),
-// one output tile of one expert per block. Tiles (Tile<>) are 256 x 256 or
-// 256 x 192 with eight waves (one block per CU) or 128 x 128 with four waves
-// (two blocks per CU); each wave accumulates its sub-tile with
-// v_mfma_f32_32x32x16_bf16 in f32. Operands reach LDS through buffer loads
-// that write LDS directly (16 bytes per lane, out-of-range offsets read as
-// zero, so ragged tails need no branch) into a ring of 2-4 stages; the next
-// stages' loads stay in flight across the barrier (partial vmcnt waits).
+// one output tile of one expert per block. The tiles of nearly every launch
+// are 256 x 256 or 256 x 192 (PhaseTile<>, phase_tile: eight waves, one block
+// per CU, 64-deep stages taken in 64-column phases); small weight gradients
+// take 128 x 128 with four waves on a plain ring of stages (Tile<>, two blocks
+// per CU). A wave accumulates its sub-tile with v_mfma_f32_32x32x16_bf16 in
+// f32. Operands reach LDS through buffer loads that write LDS directly (16
+// bytes per lane, out-of-range offsets read as zero, so ragged tails need no
+// branch); later stages' loads stay in flight across the barriers (partial
+// vmcnt waits).
 // An operand whose k index is contiguous in HBM is stored k-major with an
 // XOR chunk swizzle; one whose k index is strided (weights read transposed
 // in the backward, the token-reduced weight-gradient GEMMs) is copied
@@ -93,10 +95,31 @@ struct GemmBatch {
 template <int EPI>
 constexpr bool compact_tiles() { return EPI != EPI_F32; }
 
+// Rows of expert e: sum over the groups, sixteen counts in flight at a time.
 __device__ __forceinline__ int expert_rows(const int32_t* counts, int G, int E, int e) {
+    constexpr int U = 16;
     int n = 0;
-    for (int g = 0; g < G; ++g) n += counts[g * E + e];
+    for (int g0 = 0; g0 < G; g0 += U) {
+        int v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = counts[min(g0 + u, G - 1) * E + e];
+#pragma unroll
+        for (int u = 0; u < U; ++u) n += g0 + u < G ? v[u] : 0;
+    }
     return n;
+}
+
+// Inclusive sum over the lanes of a wave, in DPP adds (a few cycles each; the
+// six dependent LDS shuffles of the usual form are most of a microsecond, at
+// the start of every tile).
+__device__ __forceinline__ int wave_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15, rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31, rows 2, 3
+    return v;
 }
 
 // m-tiles of an expert with ne rows: ceil(ne / bm), except that an expert
@@ -119,24 +142,15 @@ struct LiveTile {
 __device__ __forceinline__ bool live_tile(const int32_t* counts, int G, int E, int cap, int bm,
                                           int lsplit, int tiles_n, int w, LiveTile* out) {
     const int lane = threadIdx.x & 63;
-    int ne = 0;
-    if (lane < E) {
-#pragma unroll 4
-        for (int g = 0; g < G; ++g) ne += counts[g * E + lane];
-        ne = min(ne, cap);  // never past the expert's rows, whatever the counts say
-    }
+    // (never past the expert's rows, whatever the counts say)
+    const int ne = lane < E ? min(expert_rows(counts, G, E, lane), cap) : 0;
     const int t = expert_mtiles(ne, bm, lsplit) * tiles_n;
-    int incl = t;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int u = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += u;
-    }
-    if (w >= __shfl(incl, 63, 64)) return false;
+    const int incl = wave_scan(t);
+    if (w >= __builtin_amdgcn_readlane(incl, 63)) return false;
     const int e = __popcll(__ballot(incl <= w));
     out->e = e;
-    out->r = w - __shfl(incl - t, e, 64);
-    out->ne = __shfl(ne, e, 64);
+    out->r = w - __builtin_amdgcn_readlane(incl - t, e);
+    out->ne = __builtin_amdgcn_readlane(ne, e);
     return true;
 }
 
@@ -167,18 +181,13 @@ __device__ __forceinline__ bool spread_tile(const GemmBatch& batch, int bm, int 
     int ne = 0;
     if (lane < E) ne = min(expert_rows(p0.counts, p0.G, E, lane), p0.M);
     const bool heavy_l = lane < E && 2 * ne >= bm;
-    const uint64_t emask = E >= 64 ? ~0ull : (1ull << E) - 1ull;
-    const uint64_t hmask = __ballot(heavy_l) & emask;
     const int te = lane < E ? expert_mtiles(ne, bm, lsplit) * batch.tiles_n[0] : 0;
-    int nh = heavy_l ? te : 0, nl = te;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        nh += __shfl_xor(nh, o, 64);
-        nl += __shfl_xor(nl, o, 64);
-    }
-    nl -= nh;
+    // either class's experts' tile ranges end to end (inclusive scans)
+    const int th = heavy_l ? te : 0, tl = te - th;
+    const int ih = wave_scan(th), il = wave_scan(tl);
+    const int nh = __builtin_amdgcn_readlane(ih, 63), nl = __builtin_amdgcn_readlane(il, 63);
     bool heavy;
-    long long j;  // index in the class's list
+    int j;  // index in the class's list
     if (lsplit > 1) {
         const int h0 = x * nh / 8, hx = (x + 1) * nh / 8 - h0;
         heavy = c < hx;
@@ -197,22 +206,14 @@ __device__ __forceinline__ bool spread_tile(const GemmBatch& batch, int bm, int 
             heavy = false;
             ci = c - nhc;
         }
-        j = static_cast<long long>(ci) * chunk + i;
+        j = ci * chunk + i;
     }
     if (j >= (heavy ? nh : nl)) return false;
-    const uint64_t cmask = heavy ? hmask : (emask & ~hmask);
-    // the class's experts' tile ranges end to end (inclusive scan)
-    const int t = (cmask >> lane) & 1ull ? te : 0;
-    int incl = t;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int u = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += u;
-    }
+    const int t = heavy ? th : tl, incl = heavy ? ih : il;
     const int e = __popcll(__ballot(incl <= j));
     *e_out = e;
-    *r_out = static_cast<int>(j - __shfl(incl - t, e, 64));
-    *ne_out = __shfl(ne, e, 64);
+    *r_out = j - __builtin_amdgcn_readlane(incl - t, e);
+    *ne_out = __builtin_amdgcn_readlane(ne, e);
     return true;
 }
 
@@ -661,6 +662,7 @@ template <int BM_, int BN_, int WGM_, int WGN_, int KB_, int NS_, int MODE_, boo
 struct Tile {
     static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, KB = KB_, NS = NS_;
     static constexpr int MODE = MODE_;
+    static constexpr bool PHASED = false;
     // PAIR: stages are fetched two at a time (kt + 2 and kt + 3 at each even
     // kt), so the two 64-byte halves of a 128-byte k-major row segment are
     // requested back to back and share one cache-line fill
@@ -680,12 +682,38 @@ struct Tile {
     static_assert(!PAIR || (NS == 4 && MODE == STAGE_DMA), "paired fetch runs a ring of four");
 };
 
+// A 256-row tile whose 64-deep stages are worked through in PB phases, one per
+// 64-column panel of B (phase_tile below): eight waves as 4 x 2, a wave's 64
+// rows against 32 columns of the phase's panel.
+template <int PB_>
+struct PhaseTile {
+    static constexpr int PB = PB_;
+    static constexpr int BM = 256, BN = 64 * PB, WGM = 4, WGN = 2, KB = 64, NS = 2;
+    static constexpr int MODE = STAGE_DMA;
+    static constexpr bool PHASED = true;
+    static constexpr int NW = 8, NT = 512, WAVES_PER_EU = 2;
+    static constexpr int WM = 64, FM = 2;
+    // LDS: two A stages, two stages of PB panels of B (panels 0, 1 and the rest
+    // in arrays of their own, so that the compiler can tell a read of one from
+    // the loads in flight into another), the epilogue's 4 KB a wave
+    static constexpr int A_EL = BM * KB, P_EL = 64 * KB, S_EL = NW * 2048;
+    static constexpr int BL_EL = 2 * P_EL, BH_EL = (PB - 2) * P_EL;
+};
+
+// The shape a phased kernel's light tiles use (light_tile): 64-column wave
+// columns and one 32-row block, each wave's LDS in a 16 KB buffer of its own.
+template <int COLS>
+struct LightShape {
+    static constexpr int BM = 32, BN = 64 * COLS, WGM = 1, WGN = COLS, NS = 8, NW = 8, NT = 512;
+    static constexpr int WM = 32, WN = 64, FM = 1, FN = 2;
+    static constexpr int RING_BYTES = NS * 16384;
+    static constexpr bool PHASED = false;
+};
+
 // Per-GEMM static sizes derived from a tiling and the operand layouts.
 template <class T, bool A_KMAJOR, bool B_KMAJOR, int EPI>
 struct GemmCfg {
-    static constexpr int AE = stage_elems<T::BM, A_KMAJOR, T::KB, T::MODE>();
-    static constexpr int BE = stage_elems<T::BN, B_KMAJOR, T::KB, T::MODE>();
-    static constexpr int BUF_BYTES = (AE + BE) * 2;  // one stage buffer
+    static constexpr int BUF_BYTES = T::RING_BYTES / T::NS;  // one stage buffer
     static constexpr bool F32_OUT = EPI == EPI_F32;
     static constexpr int OUTS = EPI == EPI_FWD1 ? 2 : 1;
     // Epilogue staging: wave w parks its outputs in stage buffer w mod NS; IPP
@@ -926,16 +954,29 @@ typedef __attribute__((address_space(3))) v4i32 lds_v4;
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 typedef __attribute__((address_space(3))) float lds_f32;
 
-// Stage buffer i of NS as an LDS pointer (a select over values: a closure or
-// array of the buffers' addresses would sit in scratch memory)
+// The kernel's LDS arrays as the light path's buffers: the ring's stage
+// buffers, or 16 KB pieces of a phased tile's arrays (a select over values: a
+// closure or array of the buffers' addresses would sit in scratch memory)
+struct LdsArrays {
+    uint16_t *b0, *b1, *b2, *b3, *b4, *b5, *b6;
+};
 template <int NS>
-__device__ __forceinline__ lds_u16* pick_lds(int i, uint16_t* b0, uint16_t* b1, uint16_t* b2,
-                                             uint16_t* b3, uint16_t* b4) {
-    uint16_t* b = b0;
-    if (NS > 1 && i == 1) b = b1;
-    if (NS > 2 && i == 2) b = b2;
-    if (NS > 3 && i == 3) b = b3;
-    if (NS > 4 && i == 4) b = b4;
+__device__ __forceinline__ lds_u16* pick_lds(int i, const LdsArrays& a) {
+    uint16_t* b = a.b0;
+    if constexpr (NS == 8) {
+        if (i == 1) b = a.b0 + 8192;
+        if (i == 2) b = a.b1;
+        if (i == 3) b = a.b1 + 8192;
+        if (i == 4) b = a.b6;
+        if (i == 5) b = a.b6 + 8192;
+        if (i == 6) b = a.b2;
+        if (i == 7) b = a.b3;
+    } else {
+        if (NS > 1 && i == 1) b = a.b1;
+        if (NS > 2 && i == 2) b = a.b2;
+        if (NS > 3 && i == 3) b = a.b3;
+        if (NS > 4 && i == 4) b = a.b4;
+    }
     return (lds_u16*)(b);
 }
 
@@ -952,16 +993,25 @@ constexpr bool light_ok() {
 template <class T>
 __device__ __forceinline__ int light_parts(int slots) {
     if (T::WGN % 4 == 0 && slots >= 4) return 4;
+    if (T::WGN % 3 == 0 && slots >= 3) return 3;
     if (T::WGN % 2 == 0 && slots >= 2) return 2;
     return 1;
 }
+
+template <class T>
+struct LightOf {
+    using type = T;
+};
+template <int PB>
+struct LightOf<PhaseTile<PB>> {
+    using type = LightShape<PB>;
+};
 
 template <class T, class CFG, bool B_KMAJOR, int EPI, int GS>
 __device__ __forceinline__ void light_tile(const GemmArgs& p, __amdgpu_buffer_rsrc_t ra_rs,
                                            __amdgpu_buffer_rsrc_t rb_rs, int e, int M, int N,
                                            int K, int m0, int n0, int part, int nparts,
-                                           uint16_t* buf0, uint16_t* buf1, uint16_t* buf2,
-                                           uint16_t* buf3, uint16_t* buf4) {
+                                           const LdsArrays& arrays) {
     constexpr int FM = T::FM, FN = T::FN, WN = T::WN, WGN = T::WGN, NS = T::NS;
     constexpr int U = kLightGroups;
     constexpr int LD = 64 + 8;          // LDS row: 64 elements + 16 bytes (rows on other banks)
@@ -984,7 +1034,8 @@ __device__ __forceinline__ void light_tile(const GemmArgs& p, __amdgpu_buffer_rs
     const int wn = wave % WGN, n0w = nb - wn * WN;
     // slice sl takes the 64-deep k groups [g0, g1); loads past klim read zeros
     const int ng = (K + 63) / 64;
-    const int g0 = ng * sl / ks, g1 = ng * (sl + 1) / ks;
+    // (three columns leave waves past the last slice: no groups)
+    const int g0 = ng * min(sl, ks) / ks, g1 = ng * min(sl + 1, ks) / ks;
     const int klim = min(K, g1 * 64);
     // load i of a group: row (k-major) or k row (mn-major) 8 i + lane / 8,
     // elements 8 (lane % 8) .. + 7 of its 64
@@ -1036,7 +1087,7 @@ __device__ __forceinline__ void light_tile(const GemmArgs& p, __amdgpu_buffer_rs
             for (int r = 0; r < 4; ++r) lacc[j][4 * q + r] = b4[r];
         }
 
-    auto lds_buf = [=](int i) { return pick_lds<NS>(i, buf0, buf1, buf2, buf3, buf4); };
+    auto lds_buf = [=](int i) { return pick_lds<NS>(i, arrays); };
     // wave w's LDS block: stage buffer w mod NS, slot w / NS
     lds_u16* const as = lds_buf(wave % NS) + (wave / NS) * W_EL;
     lds_u16* const bs = as + A_EL;
@@ -1131,7 +1182,434 @@ __device__ __forceinline__ void light_tile(const GemmArgs& p, __amdgpu_buffer_rs
     }
     __syncthreads();  // the sums are read before the epilogue stages outputs over them
     uint16_t* const ep = (uint16_t*)(lds_buf(wave % NS));  // (an LDS pointer, seen as such)
-    gemm_epilogue<T, CFG, EPI>(p, acc, buf0, ep, 0.0f, false, e, M, N, m0, n0w, sl == 0 ? 1 : 0);
+    gemm_epilogue<T, CFG, EPI>(p, acc, arrays.b0, ep, 0.0f, false, e, M, N, m0, n0w, sl == 0 ? 1 : 0);
+}
+
+// Epilogue of a phased tile: each wave turns its accumulators into outputs
+// strip by strip (64 rows x 32 columns of panel b; f32 outputs one 32-row
+// block at a time), through 4 KB of LDS of its own, 16-byte chunks XOR-swizzled
+// by row, to be stored as 64- (bf16) or 128-byte (f32) row segments. A wave's
+// LDS accesses run in order, so no pass needs a barrier, and the operand
+// stages are not touched. The saved gelu'(H) arrives in the same row segments,
+// all strips requested before the first is used.
+template <class T, int EPI>
+__device__ __forceinline__ void phase_epilogue(const GemmArgs& p, f32x16 (&acc)[T::FM][T::PB],
+                                               float (&rsum)[T::FM], bool row_sum, uint16_t* stg,
+                                               int e, int M, int N, int m0, int n0,
+                                               int fm_live) {
+    constexpr int PB = T::PB, FM = T::FM;
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int wm = wave / T::WGN, wn = wave % T::WGN;
+    const int mr = m0 + 64 * wm, nc = n0 + 32 * wn;  // the wave's first row and column
+    if constexpr (EPI == EPI_F32) {
+        if (row_sum) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i) {
+                const float t = rsum[i] + __shfl_xor(rsum[i], 32, 64);
+                const int m = mr + 32 * i + lane;
+                if (lane < 32 && m < M) p.bsum[static_cast<size_t>(e) * M + m] = t;
+            }
+        }
+    }
+    if (fm_live == 0) return;
+    typedef __attribute__((address_space(3))) uint16_t lds_u16;
+    typedef __attribute__((address_space(3))) v4i32 lds_v4;
+    typedef int v2i32 __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(3))) v2i32 lds_v2;
+    lds_u16* const s = (lds_u16*)(stg) + wave * 2048;
+    const size_t ebase = static_cast<size_t>(e) * p.out_estride;
+    if constexpr (EPI == EPI_F32) {
+        // row r of the staged block: 8 chunks of 16 bytes
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            if (i >= fm_live) break;
+#pragma unroll
+            for (int b = 0; b < PB; ++b) {
+                const int r = lane & 31;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int c = 2 * q + (lane >> 5);
+                    const float4 v = make_float4(acc[i][b][4 * q], acc[i][b][4 * q + 1],
+                                                 acc[i][b][4 * q + 2], acc[i][b][4 * q + 3]);
+                    *reinterpret_cast<lds_v4*>(s + r * 64 + ((c ^ (r & 7)) << 3)) =
+                        __builtin_bit_cast(v4i32, v);
+                }
+                const int n = nc + 64 * b + 4 * (lane & 7);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int rr = 8 * u + (lane >> 3), m = mr + 32 * i + rr;
+                    const v4i32 v = *reinterpret_cast<lds_v4*>(
+                        s + rr * 64 + (((lane & 7) ^ (rr & 7)) << 3));
+                    // weight gradients are not read again by the layer: streaming
+                    // stores keep them from displacing cached activations
+                    if (m < M && n < N)
+                        __builtin_nontemporal_store(
+                            v, reinterpret_cast<v4i32*>(static_cast<float*>(p.out) + ebase +
+                                                        static_cast<size_t>(m) * p.ldo + n));
+                }
+            }
+        }
+    } else {
+        // lane's row segment u of a strip: row 16 u + lane / 4, chunk lane % 4
+        const int sr = lane >> 2, sc = lane & 3;
+        auto slot = [&](int r, int c) { return s + r * 32 + ((c ^ ((r >> 2) & 3)) << 3); };
+        v4i32 aux[EPI == EPI_GELU_GRAD ? PB : 1][4];
+        if constexpr (EPI == EPI_GELU_GRAD) {
+#pragma unroll
+            for (int b = 0; b < PB; ++b)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int m = mr + 16 * u + sr, n = nc + 64 * b + 8 * sc;
+                    aux[b][u] = (m < M && n < N)
+                                    ? *reinterpret_cast<const v4i32*>(
+                                          static_cast<const uint16_t*>(p.aux) + ebase +
+                                          static_cast<size_t>(m) * p.ldo + n)
+                                    : v4i32{0, 0, 0, 0};
+                }
+        }
+        // the staged strip to `dst` as row segments
+        auto rows_out = [&](int b, void* dst) {
+            const int n = nc + 64 * b + 8 * sc;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int m = mr + 16 * u + sr;
+                const v4i32 v = *reinterpret_cast<lds_v4*>(slot(16 * u + sr, sc));
+                if (m < M && n < N)
+                    *reinterpret_cast<v4i32*>(static_cast<uint16_t*>(dst) + ebase +
+                                              static_cast<size_t>(m) * p.ldo + n) = v;
+            }
+        };
+#pragma unroll
+        for (int b = 0; b < PB; ++b) {
+            uint2 dg[EPI == EPI_FWD1 ? FM : 1][4];
+            if constexpr (EPI == EPI_GELU_GRAD) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    *reinterpret_cast<lds_v4*>(slot(16 * u + sr, sc)) = aux[b][u];
+            }
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    float r[4] = {acc[i][b][4 * q], acc[i][b][4 * q + 1], acc[i][b][4 * q + 2],
+                                  acc[i][b][4 * q + 3]};
+                    lds_u16* const at = slot(32 * i + (lane & 31), q) + 4 * (lane >> 5);
+                    if constexpr (EPI == EPI_GELU_GRAD) {
+                        const v2i32 gg = *reinterpret_cast<lds_v2*>(at);
+                        r[0] *= bf16_to_f32(gg[0] & 0xFFFFu);
+                        r[1] *= __uint_as_float(gg[0] & 0xFFFF0000u);
+                        r[2] *= bf16_to_f32(gg[1] & 0xFFFFu);
+                        r[3] *= __uint_as_float(gg[1] & 0xFFFF0000u);
+                    }
+                    if constexpr (EPI == EPI_FWD1) {
+                        float g[4], d[4];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) gelu_pair(r[c], g[c], d[c]);
+                        dg[i][q] = make_uint2(pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3]));
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) r[c] = g[c];
+                    }
+                    *reinterpret_cast<lds_v2*>(at) =
+                        v2i32{static_cast<int>(pack_bf16x2(r[0], r[1])),
+                              static_cast<int>(pack_bf16x2(r[2], r[3]))};
+                }
+            rows_out(b, p.out);
+            if constexpr (EPI == EPI_FWD1) {
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        *reinterpret_cast<lds_v2*>(slot(32 * i + (lane & 31), q) +
+                                                   4 * (lane >> 5)) =
+                            v2i32{static_cast<int>(dg[i][q].x), static_cast<int>(dg[i][q].y)};
+                rows_out(b, p.out2);
+            }
+        }
+    }
+}
+
+// One tile of a PhaseTile<PB>: wave w = (wm, wn) accumulates rows 64 wm .. + 63
+// and, of every 64-column panel b, columns 32 wn .. + 31 (acc[i][b]: 32-row
+// block i). A stage is 64 deep; its phase b multiplies the wave's A fragments
+// (read once per stage) by panel b and meanwhile reads the next panel's
+// fragments, in the last phase also the next stage's A fragments, each right
+// after the last product that uses the old one.
+//
+// Every phase opens with a barrier, and a panel's LDS slot is refilled one
+// phase after its fragments were used, so the loads of a stage go out a few
+// at a time and early: with PB = 4, six phases (1.5 stages) before they
+// are read, where a ring of two whole stages issued all eight of a wave's
+// loads in one burst behind the barrier, ahead of the products, and needed
+// them back within the stage. 4 x 2 waves and 64-column panels keep every
+// row segment a whole 128-byte line in either layout (a ring of 32-deep
+// stages fetches half lines and measured 10-20% slower). Measured against
+// that ring, whose tiles were the same size: down-projection 306 -> 260 us,
+// gelu'-product 396 -> 347 at 49 000 rows over 32 experts, d = 768, f = 3072
+// (256 x 256); down-projection 140 -> 109, dxe beside the weight gradients
+// 345 -> 291 on the 17-task batch (256 x 192). Matrix products alone (no
+// loads, no LDS reads) take 156 of the 260, the rate the card holds on random
+// data; waiting for all but half of the loads in flight costs 6%, so neither
+// depth nor latency binds. Per phase a wave issues
+//   phase 0: panel PB - 1 of stage kt + 1     phase 1: panel 0, A of stage kt + 2
+//   phase b: panel b - 1 of stage kt + 2
+// and waits before phase b for what phase b reads, counting what was issued
+// after it. Fragments read in a phase are used in the next, so the barrier
+// that opens the phase after that needs no wait for LDS reads.
+template <int PB>
+struct PhaseWaits {
+    static constexpr int issued(int b) { return b == 1 ? 5 : 1; }  // wave instructions, phase b
+    static constexpr int stage() { return PB + 4; }
+    static constexpr int upto(int b) {  // of phases 0 .. b - 1
+        int n = 0;
+        for (int q = 0; q < b; ++q) n += issued(q);
+        return n;
+    }
+    // Instructions that may be in flight when phase b opens. Phase b < PB - 1
+    // reads panel b + 1 of its stage: issued in phase b + 2 of two stages
+    // before (first of that phase's instructions), or, panel PB - 1, in phase 0
+    // of the stage before. The last phase reads panel 0 and A of the next
+    // stage, issued in phase 1 of the stage before.
+    static constexpr int flight(int b) {
+        if (b == PB - 1) return stage() - upto(2) + upto(b);
+        if (b == PB - 2) return stage() - upto(1) + upto(b);
+        return (stage() - upto(b + 2) - 1) + stage() + upto(b);
+    }
+};
+
+template <class T, bool A_KMAJOR, bool B_KMAJOR, int EPI, int GS>
+__device__ __forceinline__ void phase_tile(const GemmArgs& p, __amdgpu_buffer_rsrc_t ra_rs,
+                                           __amdgpu_buffer_rsrc_t rb_rs, int e, int M, int N,
+                                           int K, int m0, int n0, int tn, uint16_t* a0,
+                                           uint16_t* a1, uint16_t* bl0, uint16_t* bh0,
+                                           uint16_t* bl1, uint16_t* bh1, uint16_t* stg) {
+    constexpr int PB = T::PB, KB = T::KB, FM = T::FM, P_EL = T::P_EL;
+    using DA = DmaStage<T::BM, A_KMAJOR, KB, T::NT>;  // four wave instructions a stage
+    using DB = DmaStage<64, B_KMAJOR, KB, T::NT>;     // one a panel
+    static_assert(DA::PER == 4 && DB::PER == 1, "stage split");
+    using W = PhaseWaits<PB>;
+    const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
+    const int wm = wave / T::WGN, wn = wave % T::WGN;
+    // 32-row blocks of the wave's rows that lie inside M
+    const int fm_live = min(FM, max(0, (M - m0 - wm * T::WM + 31) / 32));
+
+    int arow[GS == 1 ? DA::PER : 1];
+    uint32_t aoff[DA::PER], boff[PB];
+    uint32_t* const tok_s = reinterpret_cast<uint32_t*>(stg);  // k-row gather's row table
+    uint32_t bk = 0;
+    if constexpr (GS == 1) {
+#pragma unroll
+        for (int q = 0; q < DA::PER; ++q) {
+            const int r = DA::lane_row(q);
+            arow[q] = m0 + r < M ? p.tok[e * p.tok_estride + m0 + r] * p.a.ld : -1;
+        }
+        DA::lane_offs_rows(arow, aoff);
+    } else {
+        DA::lane_offs(p.a.ld, m0, M, aoff);
+    }
+    if constexpr (GS == 2) {
+        // the expert's k rows as byte offsets of their rows of x, and the
+        // sentinel past K up to the last stage that is requested
+        const int kfill = ((K + 2 * KB - 1) / (2 * KB) + 1) * 2 * KB;
+        for (int i = tid; i < kfill; i += T::NT)
+            tok_s[i] = i < K ? static_cast<uint32_t>(p.tok[e * p.tok_estride + i]) *
+                                   (2u * static_cast<uint32_t>(p.b.ld))
+                             : kGatherSentinel;
+        __syncthreads();
+    }
+#pragma unroll
+    for (int b = 0; b < PB; ++b) {
+        uint32_t o[1];
+        if constexpr (GS == 2) DB::krow_cols(n0 + 64 * b, N, o);
+        else DB::lane_offs(p.b.ld, n0 + 64 * b, N, o);
+        boff[b] = o[0];
+    }
+    const uint32_t a_step = (A_KMAJOR ? KB : KB * p.a.ld) * 2;
+    const uint32_t b_step = (B_KMAJOR ? KB : KB * p.b.ld) * 2;
+    const int nk = (K + KB - 1) / KB;
+    const int n_inside = K / KB;  // stages that lie inside K
+
+    // requests of stage kt (inside K, or any: zeros past K)
+    auto issue_a = [&](int kt, uint16_t* dst, auto inside) {
+        if constexpr (decltype(inside)::value) DA::issue_inside(ra_rs, aoff, kt * a_step, dst);
+        else if constexpr (GS == 1) DA::issue_rows(ra_rs, arow, kt * KB, K, dst);
+        else DA::issue(ra_rs, p.a.ld, m0, M, kt * KB, K, dst);
+    };
+    // panel b of stage buffer S
+    auto panel = [&](auto parity, int b) {
+        constexpr int S = decltype(parity)::value;
+        return b < 2 ? (S ? bl1 : bl0) + b * P_EL : (S ? bh1 : bh0) + (b - 2) * P_EL;
+    };
+    auto issue_b = [&](int kt, int b, auto parity, auto inside) {
+        uint32_t o[1] = {boff[b]};
+        uint16_t* const dst = panel(parity, b);
+        if constexpr (GS == 2) {
+            // panels of a stage are requested in order: its rows with panel 0
+            if (b == 0) bk = tok_s[kt * KB + DB::lane_row(0)];
+            const uint32_t ro[1] = {bk};
+            DB::issue_krows(rb_rs, ro, o, dst);
+        } else if constexpr (decltype(inside)::value) {
+            DB::issue_inside(rb_rs, o, kt * b_step, dst);
+        } else {
+            DB::issue(rb_rs, p.b.ld, n0 + 64 * b, N, kt * KB, K, dst);
+        }
+    };
+    using YES = std::true_type;
+    using NO = std::false_type;
+
+    // The bias of the wave's columns 64 b + 32 wn + 8 q + 4 (lane / 32) + 0..3
+    // starts the accumulators.
+    constexpr bool BIAS = EPI == EPI_FWD1 || EPI == EPI_BIAS;
+    uint2 bias[BIAS ? PB * 4 : 1];
+    if constexpr (BIAS) {
+#pragma unroll
+        for (int b = 0; b < PB; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int n = n0 + 64 * b + 32 * wn + 8 * q + 4 * (lane >> 5);
+                bias[b * 4 + q] = n < N ? *reinterpret_cast<const uint2*>(
+                                              static_cast<const uint16_t*>(p.bias) +
+                                              e * p.bias_estride + n)
+                                        : make_uint2(0u, 0u);
+            }
+    }
+
+    // the loop's first two stages, in the order the phases would have issued them
+    using P0 = std::integral_constant<int, 0>;
+    using P1 = std::integral_constant<int, 1>;
+    issue_b(0, 0, P0{}, NO{});
+    issue_a(0, a0, NO{});
+#pragma unroll
+    for (int b = 1; b < PB; ++b) issue_b(0, b, P0{}, NO{});
+    issue_b(1, 0, P1{}, NO{});
+    issue_a(1, a1, NO{});
+#pragma unroll
+    for (int b = 1; b < PB - 1; ++b) issue_b(1, b, P1{}, NO{});
+
+    f32x16 acc[FM][PB];
+#pragma unroll
+    for (int b = 0; b < PB; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float b4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            if constexpr (BIAS) {
+                const uint2 bb = bias[b * 4 + q];
+                b4[0] = bf16_to_f32(bb.x & 0xFFFFu);
+                b4[1] = bf16_to_f32(bb.x >> 16);
+                b4[2] = bf16_to_f32(bb.y & 0xFFFFu);
+                b4[3] = bf16_to_f32(bb.y >> 16);
+            }
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][b][4 * q + r] = b4[r];
+        }
+
+    // bias gradients: the first n-tile's waves of column half 0 also sum
+    // their A rows (dot products with ones, from the fragments)
+    const bool row_sum = EPI == EPI_F32 && p.bsum != nullptr && tn == 0 && wn == 0;
+    float rsum[FM];
+#pragma unroll
+    for (int i = 0; i < FM; ++i) rsum[i] = 0.0f;
+
+    // A and panel 0 of stage 0 have landed
+    __builtin_amdgcn_s_waitcnt(VmWait<W::flight(PB - 1) + W::issued(PB - 1)>::imm | (15 << 8));
+    ring_barrier();
+
+    auto ring = [&](auto live_blocks) {
+        constexpr int FL = decltype(live_blocks)::value;
+        bf16x8 fa[FM][4], fb[2][4];
+        auto read_a = [&](const uint16_t* as, int ks) {
+#pragma unroll
+            for (int i = 0; i < FL; ++i)
+                fa[i][ks] = read_frag<T::BM, A_KMAJOR, KB, STAGE_DMA>(as, wm * FM + i, ks, lane);
+        };
+        if constexpr (FL > 0) {
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                read_a(a0, ks);
+                fb[0][ks] = read_frag<64, B_KMAJOR, KB, STAGE_DMA>(bl0, wn, ks, lane);
+            }
+        }
+        // stage kt: A in ac, the next stage's in an; S = kt mod 2
+        auto stage = [&](int kt, uint16_t* ac, uint16_t* an, auto parity, auto inside) {
+            constexpr int S = decltype(parity)::value;
+            using NX = std::integral_constant<int, 1 - S>;
+            constexpr bool IN = decltype(inside)::value;
+            const bool live = IN || kt < nk;  // uniform
+            auto phase = [&](auto which) {
+                constexpr int b = decltype(which)::value;
+                constexpr int cur = (S * PB + b) & 1;
+                __builtin_amdgcn_s_waitcnt(VmWait<W::flight(b)>::imm | (15 << 8));
+                ring_barrier();
+                const uint16_t* bs = b < PB - 1 ? panel(parity, b + 1) : panel(NX{}, 0);
+                auto products = [&](int ks) {
+                    if constexpr (FL > 0) {
+                        if (live) {
+#pragma unroll
+                            for (int i = 0; i < FL; ++i)
+                                acc[i][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                    fb[cur][ks], fa[i][ks], acc[i][b], 0, 0, 0);
+                        }
+                    }
+                };
+                auto next_b = [&](int ks) {
+                    if constexpr (FL > 0)
+                        fb[cur ^ 1][ks] =
+                            read_frag<64, B_KMAJOR, KB, STAGE_DMA>(bs, wn, ks, lane);
+                };
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {
+                    products(ks);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (b == PB - 1) {
+                        if constexpr (EPI == EPI_F32) {
+                            if (row_sum) {
+#pragma unroll
+                                for (int i = 0; i < FL; ++i) {
+                                    const bf16x8 v = fa[i][ks];
+#pragma unroll
+                                    for (int c = 0; c < 8; ++c)
+                                        rsum[i] += static_cast<float>(v[c]);
+                                }
+                            }
+                        }
+                        read_a(an, ks);
+                        next_b(ks);
+                    } else if (ks < 2) {
+                        next_b(2 * ks);
+                        next_b(2 * ks + 1);
+                    }
+                    // this phase's requests
+                    if (ks == 0) {
+                        if constexpr (b == 0) issue_b(kt + 1, PB - 1, NX{}, inside);
+                        else issue_b(kt + 2, b - 1, parity, inside);
+                    }
+                    if constexpr (b == 1)
+                        if (ks == 1) issue_a(kt + 2, ac, inside);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            phase(std::integral_constant<int, 0>{});
+            phase(std::integral_constant<int, 1>{});
+            if constexpr (PB > 2) phase(std::integral_constant<int, 2>{});
+            if constexpr (PB > 3) phase(std::integral_constant<int, 3>{});
+        };
+        int kt = 0;
+        for (; kt + 3 < n_inside; kt += 2) {
+            stage(kt, a0, a1, P0{}, YES{});
+            stage(kt + 1, a1, a0, P1{}, YES{});
+        }
+        for (; kt < nk; kt += 2) {
+            stage(kt, a0, a1, P0{}, NO{});
+            stage(kt + 1, a1, a0, P1{}, NO{});
+        }
+    };
+    if (fm_live > 1) ring(std::integral_constant<int, 2>{});
+    else if (fm_live > 0) ring(std::integral_constant<int, 1>{});
+    else ring(std::integral_constant<int, 0>{});
+    // the requests past K have landed (here, so that no wait stands behind the stores)
+    __builtin_amdgcn_s_waitcnt(VmWait<0>::imm | (15 << 8));
+    phase_epilogue<T, EPI>(p, acc, rsum, row_sum, stg, e, M, N, m0, n0, fm_live);
 }
 
 // One BM x BN output tile of expert e per block of WGM x WGN waves, each
@@ -1157,6 +1635,27 @@ __device__ __forceinline__ void light_tile(const GemmArgs& p, __amdgpu_buffer_rs
 // GATHER = 1: operand A's rows are gathered token rows of x (the
 // up-projection fused with the dispatch); GATHER = 2: operand B's k rows are
 // (the input-weight gradient, problems with a token list).
+// Elements of the kernel's LDS arrays.
+template <class T, bool A_KMAJOR, bool B_KMAJOR, int EPI, int GATHER>
+constexpr int gemm_lds(int i) {
+    if constexpr (T::PHASED) {
+        static_assert(GATHER != 2 || (kGatherRows + 4 * T::KB) * 2 <= T::S_EL,
+                      "the gathered rows fit the epilogue's staging");
+        const int n[7] = {T::A_EL,  T::A_EL,  T::BL_EL, T::BH_EL,
+                          T::BL_EL, T::BH_EL, T::S_EL};
+        return i < 7 ? n[i] : 1;
+    } else {
+        if (i < 7) return i < T::NS ? T::RING_BYTES / T::NS / 2 : 8;
+        return GATHER == 2 ? kGatherRows + 2 * T::NS * T::KB : 1;
+    }
+}
+template <class T, bool A_KMAJOR, bool B_KMAJOR, int EPI, int GATHER>
+struct GemmLds {
+    static constexpr int n(int i) { return gemm_lds<T, A_KMAJOR, B_KMAJOR, EPI, GATHER>(i); }
+    static constexpr int B0 = n(0), B1 = n(1), B2 = n(2), B3 = n(3), B4 = n(4), B5 = n(5),
+                         B6 = n(6), TOK = n(7);
+};
+
 // (the k-row gather's token table takes the LDS of a second 4-wave block)
 template <class T, int GATHER>
 constexpr int gemm_waves_per_eu() {
@@ -1168,31 +1667,34 @@ __global__ __launch_bounds__(T::NT)
 __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu<T, GATHER>(),
                                    gemm_waves_per_eu<T, GATHER>())))
 void gemm_bf16_kernel(GemmBatch batch) {
-    using CFG = GemmCfg<T, A_KMAJOR, B_KMAJOR, EPI>;
-    constexpr int BM_ = T::BM, BN_ = T::BN, KB = T::KB, NS = T::NS, MODE = T::MODE;
-    constexpr int NT = T::NT, AE = CFG::AE, BE = CFG::BE, FM = T::FM, FN = T::FN;
-    constexpr int KSTEPS = T::KSTEPS;
-    constexpr int SZ = AE + BE;
-    constexpr int SZX = SZ > 8 ? SZ : 8;
-    __shared__ __attribute__((aligned(1024))) uint16_t buf0[SZ];
-    __shared__ __attribute__((aligned(1024))) uint16_t buf1[SZ];
-    __shared__ __attribute__((aligned(1024))) uint16_t buf2[NS > 2 ? SZX : 8];
-    __shared__ __attribute__((aligned(1024))) uint16_t buf3[NS > 3 ? SZX : 8];
-    __shared__ __attribute__((aligned(1024))) uint16_t buf4[NS > 4 ? SZX : 8];
-    // gathered k rows' byte offsets in x (padded by two rings of stages)
-    __shared__ uint32_t tok_s[GATHER == 2 ? kGatherRows + 2 * NS * KB : 1];
+    constexpr int BM_ = T::BM, BN_ = T::BN;
+    using LD = GemmLds<T, A_KMAJOR, B_KMAJOR, EPI, GATHER>;
+    __shared__ __attribute__((aligned(1024))) uint16_t buf0[LD::B0];
+    __shared__ __attribute__((aligned(1024))) uint16_t buf1[LD::B1];
+    __shared__ __attribute__((aligned(1024))) uint16_t buf2[LD::B2];
+    __shared__ __attribute__((aligned(1024))) uint16_t buf3[LD::B3];
+    __shared__ __attribute__((aligned(1024))) uint16_t buf4[LD::B4];
+    __shared__ __attribute__((aligned(1024))) uint16_t buf5[LD::B5];
+    __shared__ __attribute__((aligned(1024))) uint16_t buf6[LD::B6];
+    // gathered k rows' byte offsets in x (padded by two rings of stages; a
+    // phased tile keeps them where its epilogue stages outputs)
+    __shared__ uint32_t tok_s[LD::TOK];
 
     const int b = blockIdx.x;
     // column parts of a light expert's tiles: at most the expert's m-tile
     // slots of the grid (ceil(capacity / BM)), so the live tiles still fit it
     // (the d-wide row GEMMs: a few long tiles per expert; the f-wide ones have
     // many short light tiles already)
-    const int lsplit = light_ok<T, A_KMAJOR, B_KMAJOR, EPI>() && (EPI == EPI_BIAS || EPI == EPI_STORE)
-                           ? light_parts<T>((batch.p[0].M + BM_ - 1) / BM_)
+    using LT = typename LightOf<T>::type;
+    constexpr bool LIGHT = light_ok<LT, A_KMAJOR, B_KMAJOR, EPI>();
+    const int lsplit = LIGHT && (EPI == EPI_BIAS || EPI == EPI_STORE)
+                           ? light_parts<LT>((batch.p[0].M + BM_ - 1) / BM_)
                            : 1;
     int qe = 0, qu = 0, qn = 0, qt = 0, qne = 0;  // quota: expert, rank, units, tiles, rows
     if constexpr (SCHED == 1) {
-        __shared__ QuotaPlan qp;
+        // (in the first stage buffer, read before any stage is requested)
+        static_assert(sizeof(QuotaPlan) <= sizeof(buf0), "the plan fits the buffer");
+        QuotaPlan& qp = *reinterpret_cast<QuotaPlan*>(buf0);
         if (threadIdx.x < 64)
             build_quota_plan<EPI>(batch, BM_, lsplit, static_cast<int>(gridDim.x), &qp);
         __syncthreads();
@@ -1206,6 +1708,7 @@ void gemm_bf16_kernel(GemmBatch batch) {
         qu = __builtin_amdgcn_readfirstlane(b - qp.first[e_b]);
         qt = __builtin_amdgcn_readfirstlane(qp.tiles[e_b]);
         qne = __builtin_amdgcn_readfirstlane(qp.ne[e_b]);
+        __syncthreads();
     }
     for (int it = 0;; ++it) {
     int prob = 0, e, r, ne, tiles_m;
@@ -1297,14 +1800,23 @@ void gemm_bf16_kernel(GemmBatch batch) {
         GS == 2 ? make_rsrc(p.b.base, p.gather_bytes)
            : make_rsrc(static_cast<const uint16_t*>(p.b.base) + e * p.b.estride,
                        p.b.estride * 2);
-    if constexpr (light_ok<T, A_KMAJOR, B_KMAJOR, EPI>()) {
-        if (!p.var_k && __builtin_amdgcn_readfirstlane(M - m0) <= 32) {
-            light_tile<T, CFG, B_KMAJOR, EPI, GS>(p, ra_rs, rb_rs, e, M, N, K, m0, n0,
-                                                   parts ? tm : 0, parts ? lsplit : 1, buf0,
-                                                   buf1, buf2, buf3, buf4);
+    if constexpr (LIGHT) {
+        if (!p.var_k && M - m0 <= 32) {
+            light_tile<LT, GemmCfg<LT, A_KMAJOR, B_KMAJOR, EPI>, B_KMAJOR, EPI, GS>(
+                p, ra_rs, rb_rs, e, M, N, K, m0, n0, parts ? tm : 0, parts ? lsplit : 1,
+                LdsArrays{buf0, buf1, buf2, buf3, buf4, buf5, buf6});
             return true;
         }
     }
+    if constexpr (T::PHASED) {
+        phase_tile<T, A_KMAJOR, B_KMAJOR, EPI, GS>(p, ra_rs, rb_rs, e, M, N, K, m0, n0, tn, buf0,
+                                                   buf1, buf2, buf3, buf4, buf5, buf6);
+        return true;
+    } else {
+    using CFG = GemmCfg<T, A_KMAJOR, B_KMAJOR, EPI>;
+    constexpr int KB = T::KB, NS = T::NS, MODE = T::MODE;
+    constexpr int NT = T::NT, AE = stage_elems<BM_, A_KMAJOR, KB, MODE>(), FM = T::FM, FN = T::FN;
+    constexpr int KSTEPS = T::KSTEPS;
     // Gathered A rows (the tile's rows, fixed over the k loop): each lane's
     // row offsets in x, read once. Gathered B k rows (new ones every stage):
     // the expert's token list in LDS, each lane's offsets for the next
@@ -1572,6 +2084,7 @@ void gemm_bf16_kernel(GemmBatch batch) {
     uint16_t* const ep = eb == 0 ? buf0 : eb == 1 ? buf1 : eb == 2 ? buf2 : eb == 3 ? buf3 : buf4;
     gemm_epilogue<T, CFG, EPI>(p, acc, buf0, ep, rsum, row_sum, e, M, N, m0, n0, fm_live);
     return true;
+    }
     };
     bool ran;
     if constexpr (GATHER == 0) ran = tile(std::integral_constant<int, 0>{});
@@ -1769,20 +2282,11 @@ void launch_bf16(const Dims& D, const GemmArgs& a, int grid_m_rows, int sched, h
     launch_bf16<T, AK, BK_, EPI, GATHER>(D, &a, &grid_m_rows, 1, sched, st);
 }
 
-// Tilings (BM, BN, waves, KB, stages, staging).
-using TileBig = Tile<256, 256, 2, 4, 32, 4, STAGE_DMA>;    // 8 waves, one block per CU
-using TileNarrow = Tile<256, 192, 4, 2, 64, 2, STAGE_DMA>; // 8 waves, 3/4 of TileBig's columns
-using TileSmall = Tile<128, 128, 2, 2, 32, 4, STAGE_DMA>;  // 4 waves, two blocks per CU
-// TileBig with 64-deep stages in a ring of two: half the stage barriers per
-// k, one stage in flight instead of three. For the f-wide row GEMMs (short
-// k = d, heavy epilogues) measured 1.3-1.5% faster per step at ViT-B/16 and
-// the 17-task pool and even at ViT-L/16; for the d-wide ones (k = f) the
-// forward 0.743 -> 0.722 ms at wide E = 32 and 0.312 -> 0.307 at ViT-L/16;
-// for the batched weight gradients the backward 0.629 -> 0.625 ms at
-// ViT-L/16 (no spill, against one with TileBig), the other workloads
-// unchanged. So every 256 x 256 launch takes TileDeep; TileBig (the 32-deep
-// ring of four) is the baseline these measurements and TileNarrow refer to.
-using TileDeep = Tile<256, 256, 2, 4, 64, 2, STAGE_DMA>;
+// Tilings: 256 x 256, 256 x 192 (fewer idle CUs where an output is d wide),
+// and 128 x 128 on a ring of four 32-deep stages, two blocks per CU.
+using TileBig = PhaseTile<4>;
+using TileNarrow = PhaseTile<3>;
+using TileSmall = Tile<128, 128, 2, 2, 32, 4, STAGE_DMA>;
 
 // Work of a launch in units of one CU's time: rounds of one-block-per-CU
 // waves times the tile's area (relative cost per tile area `eff`).
@@ -1793,25 +2297,26 @@ double tile_cost(long long tiles, int bm, int bn, double eff) {
 template <bool AK, bool BK_, int EPI, int GATHER = 0>
 void launch_gemm(const Dims& D, const GemmArgs& a, int grid_m_rows, int sched, hipStream_t st) {
     if (D.dtype == VMOE_BF16) {
-        // 256 x 256 tiles (half the operand bytes per flop of 128 x 128) with
-        // 64-deep stages (TileDeep) for the GEMMs whose m is the expert's rows.
+        // 256 x 256 tiles (half the operand bytes per flop of 128 x 128) for
+        // the GEMMs whose m is the expert's rows.
         // (bf16 weight gradients run batched in ffn_bwd_launch; this EPI_F32
         // case only serves other callers.)
         if constexpr (EPI == EPI_F32) {
             launch_bf16<TileSmall, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
         } else if constexpr (EPI == EPI_BIAS || EPI == EPI_STORE) {
             // Narrow outputs (N = d_model) give few tiles: 192-column tiles fill
-            // more CUs when that saves a round (two-stage 64-deep ring, a few
-            // per cent slower per tile)
+            // more CUs when that saves a round (a few per cent slower per area;
+            // the f-wide outputs have tiles enough, and 256 x 192 measured
+            // 101 -> 107 us there at ViT-B/16, 133 -> 141 on the 17-task batch)
             const long long tm = cdiv(grid_m_rows, 256);
             const double big = tile_cost(D.E * tm * cdiv(a.N, 256), 256, 256, 1.0);
             const double narrow = tile_cost(D.E * tm * cdiv(a.N, 192), 256, 192, 1.05);
             if (narrow < big)
                 launch_bf16<TileNarrow, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
             else
-                launch_bf16<TileDeep, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
+                launch_bf16<TileBig, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
         } else {
-            launch_bf16<TileDeep, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
+            launch_bf16<TileBig, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
         }
     } else {
         dim3 grid(cdiv(a.N, FT), cdiv(grid_m_rows, FT), D.E);
@@ -2031,7 +2536,7 @@ vmoe_status ffn_bwd_launch(const Dims& D, const void* xe, const int32_t* counts,
             if (narrow <= small && narrow <= big)
                 launch_bf16<TileNarrow, false, false, EPI_F32, GA>(D, both, rows_m, 2, sched, st);
             else if (big <= small)
-                launch_bf16<TileDeep, false, false, EPI_F32, GA>(D, both, rows_m, 2, sched, st);
+                launch_bf16<TileBig, false, false, EPI_F32, GA>(D, both, rows_m, 2, sched, st);
             else
                 launch_bf16<TileSmall, false, false, EPI_F32, GA>(D, both, rows_m, 2, sched, st);
         };
