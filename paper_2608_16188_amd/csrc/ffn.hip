@@ -970,7 +970,7 @@ __device__ __forceinline__ lds_u16* pick_lds(int i, const LdsArrays& a) {
         if (i == 4) b = a.b6;
         if (i == 5) b = a.b6 + 8192;
         if (i == 6) b = a.b2;
-        if (i == 7) b = a.b3;
+        if (i == 7) b = a.b4;
     } else {
         if (NS > 1 && i == 1) b = a.b1;
         if (NS > 2 && i == 2) b = a.b2;
