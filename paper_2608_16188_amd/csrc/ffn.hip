@@ -2105,6 +2105,142 @@ void gemm_bf16_kernel(GemmBatch batch) {
     }
 }
 
+// ------------------------------------------------------------------ small batches
+
+// Forward GEMMs of a layer whose expert buffers hold at most 32 RB rows (a few
+// images served at a time): C[m, n] = sum_k A[m, k] B[n, k], both k-major, for
+// all rows of one expert and 32 columns a block. Four waves split k in groups
+// of 64, two groups in flight in registers, every load a coalesced 128-byte
+// piece of a row; a group passes through LDS of the wave's own (16-byte
+// chunks XOR-swizzled by row) to be read back as fragments. The waves' sums
+// meet in LDS and are added in wave order, bias, GELU pair and rounding
+// following in f32. Bound by latency: a launch of 256 x 256 tiles gives such a
+// layer 24 to 96 CUs of work, each streaming up to 1.5 MB through one CU's
+// share of the chip's bandwidth. (Fragments loaded straight from memory, 32
+// rows an instruction, kept the address unit busy: 30 -> 46 us at 52 rows of
+// 8 experts, d = 768, f = 3072, both GEMMs.)
+template <int EPI, int RB, int GATHER>
+__global__ __launch_bounds__(256) void small_rows_kernel(GemmArgs p) {
+    static_assert(EPI == EPI_FWD1 || EPI == EPI_BIAS, "forward GEMMs");
+    constexpr int NW = 4, ROWS = 32 * RB + 32;  // staged rows: A, then B
+    constexpr int ST = ROWS * 64 * 2, PA = RB * 16 * 64 * 4;  // bytes per wave
+    __shared__ __attribute__((aligned(16))) char lds[NW * (ST > PA ? ST : PA)];
+    const int e = blockIdx.y, n0 = blockIdx.x * 32;
+    const int ne = expert_rows(p.counts, p.G, p.E, e);
+    const int M = min(ne, p.M), N = p.N, K = p.K;
+    if (M == 0) return;
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const __amdgpu_buffer_rsrc_t ra_rs =
+        GATHER ? make_rsrc(p.a.base, p.gather_bytes)
+               : make_rsrc(static_cast<const uint16_t*>(p.a.base) + e * p.a.estride,
+                           p.a.estride * 2);
+    const __amdgpu_buffer_rsrc_t rb_rs = make_rsrc(
+        static_cast<const uint16_t*>(p.b.base) + e * p.b.estride, p.b.estride * 2);
+    // load i of a group: row 8 i + lane / 8, elements 8 (lane % 8) .. + 7
+    const int lr = lane >> 3, lc = 8 * (lane & 7);
+    constexpr int LA = 4 * RB, LB = 4;
+    int arow[LA], brow[LB];  // element offsets of the lane's rows, -1 outside
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        const int m = 8 * i + lr;
+        arow[i] = m >= M ? -1 : (GATHER ? p.tok[e * p.tok_estride + m] : m) * p.a.ld;
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+        const int n = n0 + 8 * i + lr;
+        brow[i] = n < N ? n * p.b.ld : -1;
+    }
+    const int ng = (K + 63) / 64;
+    const int g0 = ng * wave / NW, g1 = ng * (wave + 1) / NW;
+    uint4 fa[2][LA], fb[2][LB];
+    auto load = [&](int u, int g) {  // (past the wave's last group nothing is read)
+        const int k = 64 * g + lc;
+        const bool in = g < g1 && k < K;
+#pragma unroll
+        for (int i = 0; i < LB; ++i)
+            fb[u][i] = buf_load16(rb_rs, in && brow[i] >= 0 ? static_cast<uint32_t>(brow[i] + k) * 2u
+                                                            : kOutOfRange);
+#pragma unroll
+        for (int i = 0; i < LA; ++i)
+            fa[u][i] = buf_load16(ra_rs, in && arow[i] >= 0 ? static_cast<uint32_t>(arow[i] + k) * 2u
+                                                            : kOutOfRange);
+    };
+    f32x16 acc[RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[i][q] = 0.0f;
+    uint16_t* const st = reinterpret_cast<uint16_t*>(lds + wave * ST);
+    auto at = [&](int r, int c) { return st + r * 64 + ((c ^ (r & 7)) << 3); };
+    load(0, g0);
+    __builtin_amdgcn_sched_barrier(0);
+    load(1, g0 + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int g = g0; g < g1; g += 2) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            // (one wave's LDS accesses run in order: the previous group's reads
+            // are done before these writes)
+#pragma unroll
+            for (int i = 0; i < LA; ++i)
+                *reinterpret_cast<uint4*>(at(8 * i + lr, lane & 7)) = fa[u][i];
+#pragma unroll
+            for (int i = 0; i < LB; ++i)
+                *reinterpret_cast<uint4*>(at(32 * RB + 8 * i + lr, lane & 7)) = fb[u][i];
+            __builtin_amdgcn_sched_barrier(0);
+            load(u, g + u + 2);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int c = 2 * s + (lane >> 5);
+                const bf16x8 b =
+                    *reinterpret_cast<const bf16x8*>(at(32 * RB + (lane & 31), c));
+                // (swapped operands, as everywhere: lane l holds row l % 32)
+#pragma unroll
+                for (int i = 0; i < RB; ++i)
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                        b, *reinterpret_cast<const bf16x8*>(at(32 * i + (lane & 31), c)), acc[i],
+                        0, 0, 0);
+            }
+        }
+    }
+    __syncthreads();  // every wave is done with its staged rows
+    float* const part = reinterpret_cast<float*>(lds);  // [wave][i][register][lane]
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) part[((wave * RB + i) * 16 + q) * 64 + lane] = acc[i][q];
+    __syncthreads();
+    // wave w adds row blocks and columns 8 q + 4 (l / 32) + 0..3 of row l % 32
+#pragma unroll
+    for (int t = 0; t < RB; ++t) {
+        const int i = t, q = wave;
+        const int m = 32 * i + (lane & 31), n = n0 + 8 * q + 4 * (lane >> 5);
+        if (m >= M || n >= N) continue;
+        const uint2 bb = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(p.bias) +
+                                                         e * p.bias_estride + n);
+        float v[4] = {bf16_to_f32(bb.x & 0xFFFFu), bf16_to_f32(bb.x >> 16),
+                      bf16_to_f32(bb.y & 0xFFFFu), bf16_to_f32(bb.y >> 16)};
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] += part[((w * RB + i) * 16 + 4 * q + c) * 64 + lane];
+        const size_t o = e * p.out_estride + static_cast<size_t>(m) * p.ldo + n;
+        if constexpr (EPI == EPI_FWD1) {
+            float dg[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float h = v[c];
+                gelu_pair(h, v[c], dg[c]);
+            }
+            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out2) + o) =
+                make_uint2(pack_bf16x2(dg[0], dg[1]), pack_bf16x2(dg[2], dg[3]));
+        }
+        *reinterpret_cast<uint2*>(static_cast<uint16_t*>(p.out) + o) =
+            make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+    }
+}
+
 // ------------------------------------------------------------------ f32 FMA path
 
 // f32 activations: 64 x 64 output tiles, four waves, each a 32 x 32 block on
@@ -2296,6 +2432,24 @@ double tile_cost(long long tiles, int bm, int bn, double eff) {
 
 template <bool AK, bool BK_, int EPI, int GATHER = 0>
 void launch_gemm(const Dims& D, const GemmArgs& a, int grid_m_rows, int sched, hipStream_t st) {
+    // Few rows an expert, and so few tiles that a quarter of the CUs or more
+    // would have none: small code over many blocks instead. Expert MLP forward
+    // at d = 768, f = 3072, 52 rows: E = 8 (96 and 32 tiles) 48.5 -> 29.5 us,
+    // E = 12 50.8 -> 45.3, E = 16 (192 and 64 tiles) 52.0 -> 49.9, E = 32 even;
+    // E = 64 at d = 512, f = 2048 slower (80 -> 93), and with 103 rows at
+    // E = 8 too (51 -> 54: the blocks read an expert's rows over and over).
+    // (Independent of `sched`: an expert is one tile, there is nothing to share.)
+    if constexpr (EPI == EPI_FWD1 || EPI == EPI_BIAS) {
+        if (D.dtype == VMOE_BF16 && grid_m_rows <= 64 &&
+            static_cast<long long>(D.E) * cdiv(a.N, 256) <= kNumCUs * 3 / 4) {
+            const dim3 grid(cdiv(a.N, 32), D.E);
+            if (grid_m_rows <= 32)
+                small_rows_kernel<EPI, 1, GATHER><<<grid, 256, 0, st>>>(a);
+            else
+                small_rows_kernel<EPI, 2, GATHER><<<grid, 256, 0, st>>>(a);
+            return;
+        }
+    }
     if (D.dtype == VMOE_BF16) {
         // 256 x 256 tiles (half the operand bytes per flop of 128 x 128) for
         // the GEMMs whose m is the expert's rows.

@@ -37,6 +37,12 @@ CASES = [
     (512, 128, [600, 20, 1]),
     (448, 128, [900, 9, 32]),
     (192, 64, [700, 30]),
+    # buffers of at most 64 and 32 rows: the small-batch forward
+    (72, 200, [64, 1, 33, 0, 63, 32]),
+    (520, 136, [32, 31, 0, 2]),
+    (768, 264, [52, 40, 64]),
+    # two m-tiles an expert, rows split evenly
+    (136, 328, [257, 320, 321, 448, 512]),
 ]
 # 16 and more experts: dxe beside the weight gradients
 MANY = (200, 520, [0, 1, 7, 32, 33, 34, 63, 64, 65, 100, 127, 128, 129, 200, 255, 256, 257])
