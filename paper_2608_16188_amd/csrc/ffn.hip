@@ -28,9 +28,9 @@
 // XCD's L2. The tile shape is chosen per launch by a cost model: rounds of
 // 256 CUs times the tile area, scaled by a per-shape efficiency.
 //
-// f32 path: 64 x 64 tiles on the f32 matrix cores (v_mfma_f32_32x32x2f32, one
-// 32 x 32 block per wave) with coalesced operand staging through LDS and the
-// same operand and epilogue description (the accuracy path).
+// f32 path: 32 x 32 or 64 x 64 tiles on the f32 matrix cores
+// (v_mfma_f32_32x32x2f32), four waves splitting k, operands straight from
+// memory, with the same operand and epilogue description (the accuracy path).
 #include <mutex>
 #include <type_traits>
 
@@ -67,7 +67,7 @@ struct GemmArgs {
     const void* bias;       // EPI_FWD1 / EPI_BIAS
     long long bias_estride;
     const void* aux;        // EPI_GELU_GRAD: saved gelu'(H)
-    float* bsum;            // EPI_F32 (bf16 path): row sums of A per expert, or null
+    float* bsum;            // EPI_F32: row sums of A per expert, or null
     // Gathered operand (kernels built with GATHER != 0): the operand's rows
     // are token rows of x, row r of expert e being x[tok[e * tok_estride + r]];
     // its base is x itself (estride 0) and gather_bytes the size of x.
@@ -2248,60 +2248,104 @@ __global__ __launch_bounds__(256) void small_rows_kernel(GemmArgs p) {
     }
 }
 
-// ------------------------------------------------------------------ f32 FMA path
+// ------------------------------------------------------------------ f32 path
 
-// f32 activations: 64 x 64 output tiles, four waves, each a 32 x 32 block on
-// v_mfma_f32_32x32x2_f32 (f32 products and sums); FK-deep k stages staged in
-// LDS as [k][mn] (rows padded by one float), read so that consecutive
-// threads load consecutive addresses whatever the operand's layout.
-constexpr int FT = 64, FK = 32;
-typedef float f32x16_f __attribute__((ext_vector_type(16)));
+// f32 activations: a block computes a 32 FB x 32 FB output tile of one expert
+// with four waves that split k (whole runs of eight); every wave multiplies
+// the whole tile over its share on v_mfma_f32_32x32x2_f32 (f32 products and
+// sums), and the four partial tiles are added in wave order through LDS before
+// the epilogue. A step is 32 deep. Of each eight k, lane l supplies row
+// l % 32 and the four of half l / 32, in both operands. A k-major operand is
+// read as 128-byte pieces of rows (16 bytes a lane) and passes through LDS of
+// the wave's own, the next step's loads in flight meanwhile; an mn-major one is
+// read straight into fragments, four coalesced dwords a run. No barrier stands
+// before the partial tiles. Such a layer is bound by latency: the former
+// 64 x 64 tiles of four waves side by side left the d-wide products of 788
+// tokens (d = 192, f = 768, E = 8) on 96 blocks, each walking all 768 k behind
+// two barriers a stage (30 and 36 us), and the bias gradients in two launches
+// of 14 us, which the weight gradients' first n-tile now sums from its
+// fragments. (k-major fragments straight from memory, 32 rows an instruction:
+// forward 47 us against 50 before, 67 against 53 at d = 200, f = 800.) Layer step
+// of the 788 tokens 219 -> 133 us, expert MLP forward 50 -> 29, backward
+// 121 -> 57; 1576 tokens, k = 3, d = 384, f = 1536, E = 16: 201 -> 153, 441 -> 340.
+constexpr int kF32Waves = 4;
+constexpr int kF32Ld = 32 + 4;  // LDS row: 32 k and 16 bytes (rows on other banks)
 
-template <bool KMAJOR>
-__device__ __forceinline__ float f32_elem(const float* base, int ld, int mn, int k) {
-    return KMAJOR ? base[static_cast<size_t>(mn) * ld + k] : base[static_cast<size_t>(k) * ld + mn];
-}
-
-// One FK x FT operand stage (zero outside the operand), in two halves: the
-// loads into registers, then the stores into S[k][mn]. k-major operands are
-// walked k fastest, mn-major ones mn fastest.
-constexpr int kF32Per = FK * FT / 256;
-
-template <bool KMAJOR>
-__device__ __forceinline__ void load_f32(float (&v)[kF32Per], const float* base, int ld, int mn0,
-                                         int mn_lim, int k0, int k_lim) {
+// k rows k .. k + 3 of one column of an mn-major operand, zero from kend (>= 1).
+__device__ __forceinline__ float4 f32_cols(const float* col, int ld, int k, int kend) {
+    float v[4];
 #pragma unroll
-    for (int u = 0; u < kF32Per; ++u) {
-        const int q = u * 256 + static_cast<int>(threadIdx.x);
-        const int kk = KMAJOR ? q % FK : q / FT, mn = KMAJOR ? q / FK : q % FT;
-        v[u] = (mn0 + mn < mn_lim && k0 + kk < k_lim) ? f32_elem<KMAJOR>(base, ld, mn0 + mn, k0 + kk)
-                                                      : 0.0f;
-    }
+    for (int j = 0; j < 4; ++j)
+        v[j] = col[static_cast<size_t>(min(k + j, kend - 1)) * ld];
+    return make_float4(k < kend ? v[0] : 0.0f, k + 1 < kend ? v[1] : 0.0f,
+                       k + 2 < kend ? v[2] : 0.0f, k + 3 < kend ? v[3] : 0.0f);
 }
 
-template <bool KMAJOR>
-__device__ __forceinline__ void store_f32(float (*S)[FT + 1], const float (&v)[kF32Per]) {
+// One operand of a wave: 32 FB rows, a step in flight. Rows past `lim` read the
+// last one (their outputs are never stored).
+// (RUNS: runs of eight k a step, 4 where an operand is k-major).
+template <bool KMAJOR, int FB, int RUNS>
+struct F32Operand {
+    static_assert(!KMAJOR || RUNS == 4, "128-byte row pieces");
+    const float* p[KMAJOR ? 4 * FB : FB];
+    float4 v[RUNS * FB];  // the step in flight
+    int ld;
+    __device__ __forceinline__ void init(const float* base, int ld_, int mn0, int lim, int lane) {
+        ld = ld_;
+        if constexpr (KMAJOR) {
 #pragma unroll
-    for (int u = 0; u < kF32Per; ++u) {
-        const int q = u * 256 + static_cast<int>(threadIdx.x);
-        const int kk = KMAJOR ? q % FK : q / FT, mn = KMAJOR ? q / FK : q % FT;
-        S[kk][mn] = v[u];
+            for (int i = 0; i < 4 * FB; ++i)
+                p[i] = base + static_cast<size_t>(min(mn0 + 8 * i + (lane >> 3), lim - 1)) * ld +
+                       4 * (lane & 7);
+        } else {
+#pragma unroll
+            for (int i = 0; i < FB; ++i) p[i] = base + min(mn0 + 32 * i + (lane & 31), lim - 1);
+        }
     }
-}
+    // request the step at k, zero from kend (a multiple of 8 for a k-major operand)
+    __device__ __forceinline__ void load(int k, int kend, int lane) {
+#pragma unroll
+        for (int i = 0; i < RUNS * FB; ++i) {
+            if constexpr (KMAJOR) {
+                const bool in = k + 4 * (lane & 7) < kend;
+                v[i] = *reinterpret_cast<const float4*>(p[i] + (in ? k : -4 * (lane & 7)));
+                if (!in) v[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            } else {
+                v[i] = f32_cols(p[i % FB], ld, k + 8 * (i / FB) + 4 * (lane >> 5), kend);
+            }
+        }
+    }
+    __device__ __forceinline__ void stage(float* s, int lane) const {
+        if constexpr (KMAJOR) {
+#pragma unroll
+            for (int i = 0; i < 4 * FB; ++i)
+                *reinterpret_cast<float4*>(s + (8 * i + (lane >> 3)) * kF32Ld + 4 * (lane & 7)) =
+                    v[i];
+        }
+    }
+    // run u's fragment of row block i: from LDS, or of the held step `h`
+    __device__ __forceinline__ float4 frag(const float* s, const float4* h, int u, int i,
+                                           int lane) const {
+        if constexpr (KMAJOR)
+            return *reinterpret_cast<const float4*>(s + (32 * i + (lane & 31)) * kF32Ld + 8 * u +
+                                                    4 * (lane >> 5));
+        else
+            return h[u * FB + i];
+    }
+};
 
-// A barrier that waits for this wave's LDS accesses only: the next stage's
-// global loads stay in flight across it.
-__device__ __forceinline__ void f32_lds_barrier() {
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0); vmcnt, expcnt not waited for
-    __builtin_amdgcn_s_barrier();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-
-template <bool A_KMAJOR, bool B_KMAJOR, int EPI>
+template <bool A_KMAJOR, bool B_KMAJOR, int EPI, int FB>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p) {
-    __shared__ float As[FK][FT + 1];
-    __shared__ float Bs[FK][FT + 1];
+    constexpr int FT = 32 * FB;
+    // Two mn-major operands of 64 x 64 tiles: eight k a step, so that the
+    // registers leave room for more waves
+    constexpr int RUNS = !A_KMAJOR && !B_KMAJOR && FB == 2 ? 1 : 4;
+    // a wave's staging of its k-major operands; afterwards the partial tiles
+    constexpr int OP_EL = FT * kF32Ld, W_EL = ((A_KMAJOR ? 1 : 0) + (B_KMAJOR ? 1 : 0)) * OP_EL;
+    constexpr int STG = kF32Waves * W_EL, PART = kF32Waves * 32 * FT;
+    __shared__ __attribute__((aligned(16))) float lds[STG > PART ? STG : PART];
+    __shared__ float rpart[EPI == EPI_F32 ? kF32Waves : 1][EPI == EPI_F32 ? FT : 1];
+    float (*part)[32][FT] = reinterpret_cast<float (*)[32][FT]>(lds);
     const int e = blockIdx.z;
     const int ne = expert_rows(p.counts, p.G, p.E, e);
     const int M = p.var_k ? p.M : min(ne, p.M);
@@ -2309,78 +2353,137 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p) {
     const int N = p.N;
     const int m0 = blockIdx.y * FT, n0 = blockIdx.x * FT;
     if (m0 >= M) return;
-    const float* A = static_cast<const float*>(p.a.base) + e * p.a.estride;
-    const float* B = static_cast<const float*>(p.b.base) + e * p.b.estride;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, wm = w >> 1, wn = w & 1;
+    const int lane = threadIdx.x & 63, w = wave_id();
     const int r = lane & 31, kh = lane >> 5;
-    f32x16_f acc;
+    // the wave's share of k, in runs of eight
+    const int runs = (K + 7) / 8;
+    const int k0 = 8 * (runs * w / kF32Waves);
+    const int kend = min(K, 8 * (runs * (w + 1) / kF32Waves));
+    const bool row_sum = EPI == EPI_F32 && p.bsum != nullptr && blockIdx.x == 0;
+    float rs[FB];
+    f32x16 acc[FB][FB];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-    // the next stage's loads are issued before this stage's products and
-    // land in registers while they run
-    float va[kF32Per], vb[kF32Per];
-    load_f32<A_KMAJOR>(va, A, p.a.ld, m0, M, 0, K);
-    load_f32<B_KMAJOR>(vb, B, p.b.ld, n0, N, 0, K);
-    for (int k0 = 0; k0 < K; k0 += FK) {
-        store_f32<A_KMAJOR>(As, va);
-        store_f32<B_KMAJOR>(Bs, vb);
-        f32_lds_barrier();
-        if (k0 + FK < K) {
-            load_f32<A_KMAJOR>(va, A, p.a.ld, m0, M, k0 + FK, K);
-            load_f32<B_KMAJOR>(vb, B, p.b.ld, n0, N, k0 + FK, K);
+    for (int i = 0; i < FB; ++i) {
+        rs[i] = 0.0f;
+#pragma unroll
+        for (int j = 0; j < FB; ++j)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;
+    }
+    if (k0 < kend) {
+        float* const as = lds + w * W_EL;
+        float* const bs = as + (A_KMAJOR ? OP_EL : 0);
+        F32Operand<A_KMAJOR, FB, RUNS> oa;
+        F32Operand<B_KMAJOR, FB, RUNS> ob;
+        oa.init(static_cast<const float*>(p.a.base) + e * p.a.estride, p.a.ld, m0, M, lane);
+        ob.init(static_cast<const float*>(p.b.base) + e * p.b.estride, p.b.ld, n0, N, lane);
+        oa.load(k0, kend, lane);
+        ob.load(k0, kend, lane);
+        for (int k = k0; k < kend; k += 8 * RUNS) {
+            // (one wave's LDS accesses run in order: the last step's fragment
+            // reads are done first)
+            oa.stage(as, lane);
+            ob.stage(bs, lane);
+            float4 ha[A_KMAJOR ? 1 : RUNS * FB], hb[B_KMAJOR ? 1 : RUNS * FB];
+            if constexpr (!A_KMAJOR) {
+#pragma unroll
+                for (int i = 0; i < RUNS * FB; ++i) ha[i] = oa.v[i];
+            }
+            if constexpr (!B_KMAJOR) {
+#pragma unroll
+                for (int i = 0; i < RUNS * FB; ++i) hb[i] = ob.v[i];
+            }
+            if (k + 8 * RUNS < kend) {
+                oa.load(k + 8 * RUNS, kend, lane);
+                ob.load(k + 8 * RUNS, kend, lane);
+            }
+#pragma unroll
+            for (int u = 0; u < RUNS; ++u) {
+                if (k + 8 * u >= kend) break;  // uniform
+                float4 a[FB], b[FB];
+#pragma unroll
+                for (int i = 0; i < FB; ++i) {
+                    a[i] = oa.frag(as, ha, u, i, lane);
+                    b[i] = ob.frag(bs, hb, u, i, lane);
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int i = 0; i < FB; ++i) {
+                        const float av = t == 0 ? a[i].x : t == 1 ? a[i].y : t == 2 ? a[i].z : a[i].w;
+                        if constexpr (EPI == EPI_F32) rs[i] += av;
+#pragma unroll
+                        for (int j = 0; j < FB; ++j) {
+                            const float bv =
+                                t == 0 ? b[j].x : t == 1 ? b[j].y : t == 2 ? b[j].z : b[j].w;
+                            acc[i][j] =
+                                __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
+                        }
+                    }
+            }
         }
-        // A[m][k = 2 s + kh], B[k][n]: lane l supplies row / column l % 32
-#pragma unroll
-        for (int s2 = 0; s2 < FK / 2; ++s2)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[2 * s2 + kh][32 * wm + r],
-                                                       Bs[2 * s2 + kh][32 * wn + r], acc, 0, 0, 0);
-        f32_lds_barrier();
     }
-    // register i of lane l: row 8 (i / 4) + 4 (l / 32) + i % 4, column l % 32
-    const int n = n0 + 32 * wn + r;
+    __syncthreads();  // every wave is past its staging: the partial tiles go there
+
+    float* out = static_cast<float*>(p.out);
+    const float* bias = static_cast<const float*>(p.bias);
+    if constexpr (EPI == EPI_F32) {
+        if (row_sum) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int m = m0 + 32 * wm + 8 * (i / 4) + 4 * kh + (i % 4);
-        if (m >= M || n >= N) continue;
-        const size_t o = e * p.out_estride + static_cast<size_t>(m) * p.ldo + n;
-        float v = acc[i];
-        float* out = static_cast<float*>(p.out);
-        if (EPI == EPI_FWD1 || EPI == EPI_BIAS)
-            v += static_cast<const float*>(p.bias)[e * p.bias_estride + n];
-        if (EPI == EPI_GELU_GRAD) v *= static_cast<const float*>(p.aux)[o];
-        if (EPI == EPI_FWD1) {
-            out[o] = gelu_f(v);
-            static_cast<float*>(p.out2)[o] = gelu_grad_f(v);
-        } else {
-            out[o] = v;
+            for (int i = 0; i < FB; ++i) {
+                const float t = rs[i] + __shfl_xor(rs[i], 32, 64);
+                if (lane < 32) rpart[w][32 * i + r] = t;
+            }
         }
     }
-}
-
-// ------------------------------------------------------------------ bias gradients
-
-// out[e, c] = sum over the n_e rows of src[e, r, c]; 64 columns x 4 row phases
-// per block, phases added in a fixed order.
-template <typename T>
-__global__ __launch_bounds__(256) void colsum_kernel(const T* __restrict__ src,
-                                                     long long estride, int cols,
-                                                     const int32_t* __restrict__ counts, int G,
-                                                     int E, float* __restrict__ out) {
-    __shared__ float part[4][64];
-    const int e = blockIdx.y;
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int ph = threadIdx.x >> 6;
-    const int ne = expert_rows(counts, G, E, e);
-    float s = 0.0f;
-    if (c < cols) {
-        const T* p = src + e * estride + c;
-        for (int r = ph; r < ne; r += 4) s += Elem<T>::load(p, static_cast<size_t>(r) * cols);
+#pragma unroll
+    for (int i = 0; i < FB; ++i) {
+        if (i > 0) __syncthreads();
+        // register q of lane l: row 8 (q / 4) + 4 (l / 32) + q % 4, column l % 32
+#pragma unroll
+        for (int j = 0; j < FB; ++j)
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+                part[w][8 * (q / 4) + 4 * kh + (q % 4)][32 * j + r] = acc[i][j][q];
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < FB; ++u) {
+            const int v = u * 256 + static_cast<int>(threadIdx.x);
+            const int row = v / (FT / 4), col = 4 * (v % (FT / 4));
+            const int m = m0 + 32 * i + row, n = n0 + col;
+            if (m >= M || n >= N) continue;
+            float4 t = *reinterpret_cast<const float4*>(&part[0][row][col]);
+            float x[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+            for (int w2 = 1; w2 < kF32Waves; ++w2) {
+                t = *reinterpret_cast<const float4*>(&part[w2][row][col]);
+                x[0] += t.x; x[1] += t.y; x[2] += t.z; x[3] += t.w;
+            }
+            const size_t o = e * p.out_estride + static_cast<size_t>(m) * p.ldo + n;
+            if constexpr (EPI == EPI_FWD1 || EPI == EPI_BIAS) {
+                t = *reinterpret_cast<const float4*>(bias + e * p.bias_estride + n);
+                x[0] += t.x; x[1] += t.y; x[2] += t.z; x[3] += t.w;
+            }
+            if constexpr (EPI == EPI_GELU_GRAD) {
+                t = *reinterpret_cast<const float4*>(static_cast<const float*>(p.aux) + o);
+                x[0] *= t.x; x[1] *= t.y; x[2] *= t.z; x[3] *= t.w;
+            }
+            if constexpr (EPI == EPI_FWD1) {
+                *reinterpret_cast<float4*>(static_cast<float*>(p.out2) + o) =
+                    make_float4(gelu_grad_f(x[0]), gelu_grad_f(x[1]), gelu_grad_f(x[2]),
+                                gelu_grad_f(x[3]));
+#pragma unroll
+                for (int c = 0; c < 4; ++c) x[c] = gelu_f(x[c]);
+            }
+            *reinterpret_cast<float4*>(out + o) = make_float4(x[0], x[1], x[2], x[3]);
+        }
+        if constexpr (EPI == EPI_F32) {
+            const int t = threadIdx.x;
+            if (row_sum && i == 0 && t < FT && m0 + t < M)
+                p.bsum[static_cast<size_t>(e) * M + m0 + t] =
+                    ((rpart[0][t] + rpart[1][t]) + rpart[2][t]) + rpart[3][t];
+        }
     }
-    part[ph][threadIdx.x & 63] = s;
-    __syncthreads();
-    if (ph == 0 && c < cols)
-        out[static_cast<size_t>(e) * cols + c] = ((part[0][c & 63] + part[1][c & 63]) +
-                                                  part[2][c & 63]) + part[3][c & 63];
 }
 
 constexpr int kNumCUs = 256;
@@ -2480,8 +2583,21 @@ void launch_gemm(const Dims& D, const GemmArgs& a, int grid_m_rows, int sched, h
             launch_bf16<TileBig, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
         }
     } else {
-        dim3 grid(cdiv(a.N, FT), cdiv(grid_m_rows, FT), D.E);
-        gemm_f32_kernel<AK, BK_, EPI><<<grid, 256, 0, st>>>(a);
+        // 64 x 64 tiles halve the operand loads a product, 32 x 32 ones give a
+        // launch four times the blocks and the waves more registers: with 64
+        // from three blocks a CU on for the weight gradients (two mn-major
+        // operands; backward at 400 tokens, d = 256, f = 1024, E = 16: 55 us
+        // against 61 with 32) and from twelve on for the others (from three on:
+        // forward 101 -> 111, backward 227 -> 236 at 1576 tokens, d = 384,
+        // f = 1536, E = 8)
+        const long long big = static_cast<long long>(D.E) * cdiv(grid_m_rows, 64) * cdiv(a.N, 64);
+        if (big >= kNumCUs * (EPI == EPI_F32 ? 3 : 12)) {
+            const dim3 grid(cdiv(a.N, 64), cdiv(grid_m_rows, 64), D.E);
+            gemm_f32_kernel<AK, BK_, EPI, 2><<<grid, 256, 0, st>>>(a);
+        } else {
+            const dim3 grid(cdiv(a.N, 32), cdiv(grid_m_rows, 32), D.E);
+            gemm_f32_kernel<AK, BK_, EPI, 1><<<grid, 256, 0, st>>>(a);
+        }
     }
 }
 
@@ -2492,8 +2608,6 @@ GemmArgs base_args(const Dims& D, const int32_t* counts) {
     a.E = D.E;
     return a;
 }
-
-size_t esize(const Dims& D) { return D.dtype == VMOE_BF16 ? 2 : 4; }
 
 // A second stream per GPU (default priority, non-blocking) and two events,
 // made on first use, for launches that may run beside the caller's stream:
@@ -2657,7 +2771,7 @@ vmoe_status ffn_bwd_launch(const Dims& D, const void* xe, const int32_t* counts,
     w.out = dw2;
     w.out_estride = static_cast<long long>(D.d) * D.f;
     w.ldo = D.f;
-    w.bsum = D.dtype == VMOE_BF16 ? db2 : nullptr;  // db2 = row sums of dye^T
+    w.bsum = db2;  // db2 = row sums of dye^T
     // dW1 [f, d] = dH^T xe
     GemmArgs v = base_args(D, counts);
     v.var_k = 1;
@@ -2669,7 +2783,7 @@ vmoe_status ffn_bwd_launch(const Dims& D, const void* xe, const int32_t* counts,
     v.out = dw1;
     v.out_estride = static_cast<long long>(D.f) * D.d;
     v.ldo = D.d;
-    v.bsum = D.dtype == VMOE_BF16 ? db1 : nullptr;  // db1 = row sums of dH^T
+    v.bsum = db1;  // db1 = row sums of dH^T
     if (row_token != nullptr) {
         // xe rows gathered from x: row r of expert e is x[row_token[e, r]]
         v.b = Operand{xe, 0, D.d};
@@ -2714,13 +2828,6 @@ vmoe_status ffn_bwd_launch(const Dims& D, const void* xe, const int32_t* counts,
             hipStreamWaitEvent(st, side.join, 0) != hipSuccess)
             return VMOE_ERR_HIP;
         if (ls != VMOE_OK) return ls;
-    }
-    // bias gradients (the bf16 path sums them inside the dW GEMMs)
-    if (D.dtype == VMOE_F32) {
-        colsum_kernel<float><<<dim3(cdiv(D.d, 64), D.E), 256, 0, st>>>(
-            static_cast<const float*>(dye), rows * D.d, D.d, counts, D.G, D.E, db2);
-        colsum_kernel<float><<<dim3(cdiv(D.f, 64), D.E), 256, 0, st>>>(
-            static_cast<const float*>(dh), rows * D.f, D.f, counts, D.G, D.E, db1);
     }
     return launch_status();
 }

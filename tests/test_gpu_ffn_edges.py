@@ -11,7 +11,9 @@ Bound per element: an f32 sum of K exact products lies within
 gamma_K sum |a b| of the exact one (gamma_K ~ K 2^-24; K + 8 here for the bias
 and partial sums), a bf16 result is rounded once more (2^-9, and 2^-8 is
 allowed). gelu and gelu' of a value off by b are off by at most 1.13 b and
-0.8 b (the largest |gelu'| and |gelu''|) and by their own error, 1e-6.
+0.8 b (the largest |gelu'| and |gelu''|) and by their own error, 1e-6. f32
+layers (32 x 32 and 64 x 64 tiles, four waves splitting k) are held to the same
+bounds without the bf16 rounding.
 """
 import numpy as np
 import pytest
@@ -46,6 +48,16 @@ CASES = [
 ]
 # 16 and more experts: dxe beside the weight gradients
 MANY = (200, 520, [0, 1, 7, 32, 33, 34, 63, 64, 65, 100, 127, 128, 129, 200, 255, 256, 257])
+# f32 layers: k shares of no, one and an odd number of 8-deep runs, tiles of 32
+# and (enough of them in a launch) of 64
+F32_CASES = [
+    (8, 40, [1, 31, 32, 33, 0, 64, 65]),
+    (72, 200, [7, 8, 9, 0, 63, 100]),
+    (192, 768, [197, 200, 3, 0, 160, 161, 129, 96]),
+    (512, 1032, [40, 64, 65, 0, 7, 33, 1, 30]),
+    (72, 3080, [512, 500, 449, 0, 64, 65, 480, 1]),
+    (3080, 40, [512, 500, 449, 0, 64, 65, 480, 1]),
+]
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -67,21 +79,35 @@ def _check(name, got, ref, bound):
     assert not bad.any(), (name, int(bad.sum()), float((got - ref).abs().max()))
 
 
-def _bf16(ref, bound):
+def _rounded(ref, bound):
     """Bound of a result that is rounded to bf16."""
     return bound + 2.0 ** -8 * (ref.abs() + bound)
 
 
 @pytest.mark.parametrize("d,f,rows", CASES + [MANY], ids=lambda v: str(v) if isinstance(v, int) else "")
 def test_products_at_tile_edges(d, f, rows):
-    say("ffn edges", d, f, rows)
+    _products(d, f, rows, torch.bfloat16)
+
+
+@pytest.mark.parametrize("d,f,rows", F32_CASES, ids=lambda v: str(v) if isinstance(v, int) else "")
+def test_f32_products_at_tile_edges(d, f, rows):
+    _products(d, f, rows, torch.float32)
+
+
+def _products(d, f, rows, dt):
+    say("ffn edges", d, f, rows, dt)
+
+    def _stored(ref, bound):  # a stored result: rounded once more in bf16
+        return _rounded(ref, bound) if dt == torch.bfloat16 else bound
+
     E, R = len(rows), max(rows)
-    s = V.make_shape(R * E, 1, d, f, E, 1, 1.0, V.VMOE_BF16, capacity_override=R)
+    s = V.make_shape(R * E, 1, d, f, E, 1, 1.0,
+                     V.VMOE_BF16 if dt == torch.bfloat16 else V.VMOE_F32, capacity_override=R)
     assert V.vmoe_capacity(s) == R
     gen = torch.Generator().manual_seed(d * 1000 + f)
 
     def randn(*shape, scale=1.0):
-        return (torch.randn(*shape, generator=gen) * scale).to(torch.bfloat16)
+        return (torch.randn(*shape, generator=gen) * scale).to(dt)
 
     def padded(t):
         for e, n in enumerate(rows):
@@ -93,7 +119,7 @@ def test_products_at_tile_edges(d, f, rows):
     b1, b2 = randn(E, f, scale=0.1).cuda(), randn(E, d, scale=0.1).cuda()
     counts = torch.tensor([rows], dtype=torch.int32).cuda()
 
-    def out(*shape, dtype=torch.bfloat16):
+    def out(*shape, dtype=dt):
         return torch.full(shape, 77.0, dtype=dtype, device="cuda")
 
     act, act_grad, ye = out(E, R, f), out(E, R, f), out(E, R, d)
@@ -115,14 +141,14 @@ def test_products_at_tile_edges(d, f, rows):
         H, Hb = x @ W1.T + c["b1"][e], _gamma(d) * (x.abs() @ W1.abs().T + c["b1"][e].abs())
         cdf = 0.5 * (1 + torch.erf(H * np.sqrt(0.5)))
         pdf = torch.exp(-0.5 * H * H) / np.sqrt(2 * np.pi)
-        _check("act", act[e, :n], H * cdf, _bf16(H * cdf, 1.13 * Hb + 1e-6))
-        _check("act_grad", act_grad[e, :n], cdf + H * pdf, _bf16(cdf + H * pdf, 0.8 * Hb + 1e-6))
+        _check("act", act[e, :n], H * cdf, _stored(H * cdf, 1.13 * Hb + 1e-6))
+        _check("act_grad", act_grad[e, :n], cdf + H * pdf, _stored(cdf + H * pdf, 0.8 * Hb + 1e-6))
         Y = a @ W2.T + c["b2"][e]
-        _check("ye", ye[e, :n], Y, _bf16(Y, _gamma(f) * (a.abs() @ W2.abs().T + c["b2"][e].abs())))
+        _check("ye", ye[e, :n], Y, _stored(Y, _gamma(f) * (a.abs() @ W2.abs().T + c["b2"][e].abs())))
         D = (dy @ W2) * ag
-        _check("dh", dh[e, :n], D, _bf16(D, _gamma(d) * (dy.abs() @ W2.abs()) * ag.abs()))
+        _check("dh", dh[e, :n], D, _stored(D, _gamma(d) * (dy.abs() @ W2.abs()) * ag.abs()))
         X = h @ W1
-        _check("dxe", dxe[e, :n], X, _bf16(X, _gamma(f) * (h.abs() @ W1.abs())))
+        _check("dxe", dxe[e, :n], X, _stored(X, _gamma(f) * (h.abs() @ W1.abs())))
         for name, p, q in (("dw1", h, x), ("dw2", dy, a)):
             _check(name, g[name][e], p.T @ q, _gamma(n) * (p.abs().T @ q.abs()))
         for name, p in (("db1", h), ("db2", dy)):
