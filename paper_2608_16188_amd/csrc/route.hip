@@ -809,20 +809,19 @@ __global__ __launch_bounds__(kSlotChunk) void slots_kernel(
 // steps 2-6 in one 1024-thread block, all in LDS: the same bin map and exact
 // (key, token) rank give the order (a bin member carries the key bits below
 // the bin with its token, so one LDS word decides each comparison), then the
-// slots are assigned round by round over the order in tiles of 1024
-// positions with the ballot ranks of slots_kernel; a round's running
-// per-expert totals are its demand, which gives the next round's carry.
+// slots are assigned round by round over the order with ballot ranks; a
+// round's per-expert totals are its demand, which gives the next round's carry.
 // Phases meet at LDS-only barriers, so the order and slot stores drain in
 // the background, and the gate probabilities are fetched at the start.
 constexpr int kLocalTokens = 8192;
 constexpr int kLocalAssign = 16384;
+constexpr int kDropped = 0xFFFF;  // LDS slot of a dropped assignment
 constexpr int kTokBits = 13;  // token index inside a group < 2^13
 static_assert(kLocalTokens <= (1 << kTokBits), "token index field");
 static_assert(kKeyBits - kBinBits + kTokBits <= 32, "bin member = low key bits + token");
 
-// NW > 0 (E <= 2 NW <= 16): slots from a block scan of per-thread expert
-// counts packed two 16-bit fields to a word; NW == 0: ballot tiles.
-template <int NW>
+// NB: bits of an expert's index (E <= 2^NB).
+template <int NB>
 __global__ __launch_bounds__(1024) void local_route_kernel(
     const uint32_t* __restrict__ keys, const int32_t* __restrict__ idx,
     const float* __restrict__ probs, int32_t* __restrict__ order, int32_t* __restrict__ slot,
@@ -833,15 +832,9 @@ __global__ __launch_bounds__(1024) void local_route_kernel(
     __shared__ uint32_t memb[kLocalTokens];          // bin members: low key bits << 13 | token
     __shared__ uint16_t ord_l[kLocalTokens];         // tokens by order position
     __shared__ uint8_t idx_l[kLocalAssign];          // [Ng][k] choices
-    __shared__ uint32_t kept_l[kLocalAssign / 32];   // bit t*k + r: assignment kept
     __shared__ int start[kNumBins + 1];
     __shared__ int cursor[kNumBins];                 // histogram, then fill cursors
-    __shared__ int wcnt[2][16][kMaxExperts + 1];     // per-wave expert counts, two tiles
-    __shared__ int running[kMaxExperts + 1];         // this round's earlier tiles
-    __shared__ int carry[kMaxExperts];               // min(C, earlier rounds' demand)
-    __shared__ uint32_t wtot[16][NW > 0 ? NW : 1];   // packed scan: wave totals,
-    __shared__ uint32_t wpre[16][NW > 0 ? NW : 1];   // their prefixes over waves,
-    __shared__ uint32_t btot[NW > 0 ? NW : 1];       // the block total,
+    __shared__ int wcnt[2][16][64];                  // per-wave expert counts of a round
     __shared__ uint32_t wmin[16], wmax[16];
     __shared__ BinMap map;
     const int g = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -852,14 +845,12 @@ __global__ __launch_bounds__(1024) void local_route_kernel(
     uint32_t kv[KT];
     int32_t iv[KA];
 #pragma unroll
-    for (int u = 0; u < KT; ++u) kv[u] = keys[t0 + min(u * 1024 + tid, Ng - 1)];
+    for (int u = 0; u < KT; ++u)
+        if (u * 1024 < Ng) kv[u] = keys[t0 + min(u * 1024 + tid, Ng - 1)];
 #pragma unroll
-    for (int u = 0; u < KA; ++u) iv[u] = idx[t0 * k + min(u * 1024 + tid, nk - 1)];
+    for (int u = 0; u < KA; ++u)
+        if (u * 1024 < nk) iv[u] = idx[t0 * k + min(u * 1024 + tid, nk - 1)];
     for (int b = tid; b < kNumBins; b += 1024) cursor[b] = 0;
-    for (int q = tid; q < kLocalAssign / 32; q += 1024) kept_l[q] = 0u;
-    for (int q = tid; q < 2 * 16 * (kMaxExperts + 1); q += 1024) (&wcnt[0][0][0])[q] = 0;
-    if (tid <= kMaxExperts) running[tid] = 0;
-    if (tid < kMaxExperts) carry[tid] = 0;
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
     for (int u = 0; u < KT; ++u) {
@@ -931,9 +922,11 @@ __global__ __launch_bounds__(1024) void local_route_kernel(
         uint32_t mine[KT];
         int lo_b[KT], hi_b[KT];
 #pragma unroll
-        for (int u = 0; u < KT; ++u) mine[u] = key_l[min(u * 1024 + tid, Ng - 1)];
+        for (int u = 0; u < KT; ++u)
+            if (u * 1024 < Ng) mine[u] = key_l[min(u * 1024 + tid, Ng - 1)];
 #pragma unroll
         for (int u = 0; u < KT; ++u) {
+            if (u * 1024 >= Ng) break;
             const int b = bm(mine[u]);
             lo_b[u] = start[b];
             hi_b[u] = start[b + 1];
@@ -957,11 +950,16 @@ __global__ __launch_bounds__(1024) void local_route_kernel(
                 }
                 rank += before;
                 ord_l[rank] = static_cast<uint16_t>(t);
-                order[t0 + rank] = static_cast<int32_t>(t0 + t);
             }
         }
     }
     lds_barrier();
+    // the order and, at the end, the slots go out from LDS as rows of
+    // consecutive words (scattered word stores: 4000 of 52 000 cycles more at
+    // 6304 tokens, k = 2)
+    for (int q = tid; q < Ng; q += 1024) order[t0 + q] = static_cast<int32_t>(t0 + ord_l[q]);
+    uint16_t* const slot_l = reinterpret_cast<uint16_t*>(key_l);  // [Ng][k] (the keys are done with)
+    static_assert(kLocalAssign * 2 <= sizeof(key_l) && kLocalTokens < kDropped, "slots in LDS");
     // the probabilities of the gates, needed at the very end (their latency
     // hides behind the slots); q / k as a multiply-high by ceil(2^32 / k),
     // exact for q k < 2^32
@@ -969,154 +967,80 @@ __global__ __launch_bounds__(1024) void local_route_kernel(
     float pv[KA];
 #pragma unroll
     for (int u = 0; u < KA; ++u) {
+        if (u * 1024 >= nk) break;
         const int q = min(u * 1024 + tid, nk - 1);
         const int t = k > 1 ? static_cast<int>(__umulhi(static_cast<uint32_t>(q), kinv)) : q;
         pv[u] = probs[(t0 + t) * E + idx_l[q]];
     }
-    int total = 0;  // thread e < E: demand of the rounds so far
-    if constexpr (NW > 0) {
-        // thread tid owns order positions [tid P, tid P + P), P <= 8: its
-        // per-expert counts (4-bit fields of one word) give the ranks among
-        // its own positions, and an exclusive block scan of the counts
-        // (16-bit fields, two experts per word) the ranks before them
-        // Carries and demands never exceed N_g k <= kLocalAssign < 2^16, so
-        // every thread keeps the per-expert demand of the finished rounds
-        // packed like the scan, and derives the carries itself
-        static_assert(kLocalAssign < (1 << 16), "16-bit demand fields");
-        const int P = (Ng + 1023) / 1024;
-        uint32_t done[NW];
+    // Slots, round by round. Wave w owns a contiguous share of the order in
+    // chunks of 64 positions, one a lane. Ballots of the expert's bits give
+    // lane e the chunk's positions of expert e, and a position takes its
+    // expert's from there to know its rank; lane e carries expert e's count
+    // over the wave's chunks. The waves' counts meet in LDS once a round (two
+    // buffers, so one barrier), after which lane e of every wave knows the
+    // round's demand of expert e and where its own positions start. Bound by
+    // the instructions of one CU's sixteen waves, so a wave does nothing for
+    // chunks it does not have. 6304 tokens, E = 8, k = 2: 25 700 -> 14 900 cycles
+    // against eight positions a thread, counts packed in words and scanned over
+    // the block; 4616 tokens, E = 32: 37 700 -> 15 600 against ballot tiles of 1024
+    // positions with two barriers each; 197 tokens, E = 8: 15 000 -> 6800.
+    const int nchunk = (Ng + 63) / 64, ws = __builtin_amdgcn_readfirstlane(w);
+    const int ch0 = nchunk * ws / 16, nc = nchunk * (ws + 1) / 16 - ch0;  // nc <= KT
+    uint32_t lane_bit[NB];  // ~0 where bit b of the lane is clear
 #pragma unroll
-        for (int q = 0; q < NW; ++q) done[q] = 0u;
-        const uint32_t cap = static_cast<uint32_t>(min(C, 0xFFFF));
-        for (int r = 0; r < k; ++r) {
-            // position j's expert and its rank among this thread's earlier
-            // positions, 4-bit fields of ep and rp (E <= 16, rank < 8)
-            uint64_t lc = 0;
-            uint32_t ep = 0u, rp = 0u;
-            {
-                int tt[KT];
+    for (int b = 0; b < NB; ++b) lane_bit[b] = ((lane >> b) & 1) ? 0u : ~0u;
+    int tk[KT];
 #pragma unroll
-                for (int j = 0; j < KT; ++j) tt[j] = ord_l[min(tid * P + j, Ng - 1)];
-#pragma unroll
-                for (int j = 0; j < KT; ++j) {
-                    const int e = idx_l[tt[j] * k + r];
-                    const bool act = j < P && tid * P + j < Ng;
-                    rp |= static_cast<uint32_t>((lc >> (4 * e)) & 15u) << (4 * j);
-                    ep |= static_cast<uint32_t>(e) << (4 * j);
-                    lc += act ? (1ull << (4 * e)) : 0ull;
-                }
-            }
-            // word q of this thread's counts: experts 2q, 2q + 1 in 16-bit fields
-            auto own = [&](int q) {
-                return static_cast<uint32_t>((lc >> (8 * q)) & 15u) |
-                       (static_cast<uint32_t>((lc >> (8 * q + 4)) & 15u) << 16);
-            };
-            uint32_t inc[NW];
-#pragma unroll
-            for (int q = 0; q < NW; ++q) inc[q] = own(q);
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-#pragma unroll
-                for (int q = 0; q < NW; ++q) {
-                    const uint32_t u = static_cast<uint32_t>(__shfl_up(static_cast<int>(inc[q]), o, 64));
-                    if (lane >= o) inc[q] += u;
-                }
-            }
-            if (lane == 63) {
-#pragma unroll
-                for (int q = 0; q < NW; ++q) wtot[w][q] = inc[q];
-            }
-#pragma unroll
-            for (int q = 0; q < NW; ++q) inc[q] -= own(q);  // exclusive inside the wave
-            lds_barrier();
-            if (tid < 16 * NW) {  // (wave, word): prefix over earlier waves
-                const int w2 = tid / NW, q = tid % NW;
-                uint32_t pre = 0u;
-#pragma unroll
-                for (int w3 = 0; w3 < 15; ++w3) pre += w3 < w2 ? wtot[w3][q] : 0u;
-                wpre[w2][q] = pre;
-                if (w2 == 15) btot[q] = pre + wtot[15][q];
-            }
-            lds_barrier();
-#pragma unroll
-            for (int q = 0; q < NW; ++q) inc[q] += wpre[w][q];  // exclusive over the block
-#pragma unroll
-            for (int j = 0; j < KT; ++j) {
-                const int p = tid * P + j;
-                if (j < P && p < Ng) {
-                    const int e = static_cast<int>((ep >> (4 * j)) & 15u);
-                    uint32_t word = inc[0], dw = done[0];
-#pragma unroll
-                    for (int q = 1; q < NW; ++q) {
-                        word = (e >> 1) == q ? inc[q] : word;
-                        dw = (e >> 1) == q ? done[q] : dw;
-                    }
-                    const int sh = 16 * (e & 1);
-                    const int rank = static_cast<int>((word >> sh) & 0xFFFFu) +
-                                     static_cast<int>((rp >> (4 * j)) & 15u);
-                    const int sl = static_cast<int>(min((dw >> sh) & 0xFFFFu, cap)) + rank;
-                    const int t = ord_l[p];
-                    const bool kept = sl < C;
-                    slot[(t0 + t) * k + r] = kept ? sl : -1;
-                    if (kept) atomicOr(&kept_l[(t * k + r) >> 5], 1u << ((t * k + r) & 31));
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < NW; ++q) done[q] += btot[q];
-        }
-        if (tid < E) {
-            uint32_t word = done[0];
-#pragma unroll
-            for (int q = 1; q < NW; ++q) word = (tid >> 1) == q ? done[q] : word;
-            total = static_cast<int>((word >> (16 * (tid & 1))) & 0xFFFFu);
-        }
-    } else {
-    // slots: tile i counts its waves' experts into wcnt[i & 1] (cleared while
-    // tile i - 1 was read), so a tile takes two barriers
-    const uint64_t lt_mask = (1ull << lane) - 1ull;
-    const int ntile = (Ng + 1023) / 1024;
-    int it = 0;
+    for (int j = 0; j < KT; ++j)
+        if (j < nc) tk[j] = ord_l[min((ch0 + j) * 64 + lane, Ng - 1)];
+    int total = 0;  // lane e: expert e's demand of the rounds so far
     for (int r = 0; r < k; ++r) {
-        for (int i = 0; i < ntile; ++i, ++it) {
-            const int buf = it & 1;
-            const int p = i * 1024 + tid;
-            const bool active = p < Ng;
-            const int t = active ? ord_l[p] : 0;
-            const int e = active ? idx_l[t * k + r] : kMaxExperts;
-            uint64_t same = __ballot(1);
+        int ex[KT], rk[KT];
+        int cnt = 0;  // lane e: expert e's positions in the wave's chunks so far
 #pragma unroll
-            for (int bit = 0; bit < 7; ++bit) {
-                const uint64_t bal = __ballot((e >> bit) & 1);
-                same &= ((e >> bit) & 1) ? bal : ~bal;
+        for (int j = 0; j < KT; ++j)
+            if (j < nc) ex[j] = idx_l[tk[j] * k + r];
+#pragma unroll
+        for (int j = 0; j < KT; ++j) {
+            if (j >= nc) continue;  // uniform per wave
+            const uint64_t act = __ballot((ch0 + j) * 64 + lane < Ng);
+            // the chunk's positions of expert `lane`
+            uint32_t lo = static_cast<uint32_t>(act), hi = static_cast<uint32_t>(act >> 32);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const uint64_t bal = __ballot((ex[j] >> b) & 1);
+                lo &= static_cast<uint32_t>(bal) ^ lane_bit[b];
+                hi &= static_cast<uint32_t>(bal >> 32) ^ lane_bit[b];
             }
-            const int rank_w = __popcll(same & lt_mask);
-            if (rank_w == 0) wcnt[buf][w][e] = __popcll(same);
-            lds_barrier();
-            if (active) {
-                int rank = running[e] + rank_w;
+            // a position takes its expert's count and positions from lane e
+            rk[j] = __shfl(cnt, ex[j], 64) +
+                    static_cast<int>(__builtin_amdgcn_mbcnt_hi(
+                        static_cast<uint32_t>(__shfl(static_cast<int>(hi), ex[j], 64)),
+                        __builtin_amdgcn_mbcnt_lo(
+                            static_cast<uint32_t>(__shfl(static_cast<int>(lo), ex[j], 64)), 0u)));
+            cnt += __popc(lo) + __popc(hi);
+        }
+        wcnt[r & 1][w][lane] = cnt;
+        lds_barrier();
+        // lane e: min(C, earlier rounds' demand) + the earlier waves' positions
+        int base = min(C, total);
+        {
+            int c[16];
 #pragma unroll
-                for (int w2 = 0; w2 < 16; ++w2) rank += w2 < w ? wcnt[buf][w2][e] : 0;
-                const int sl = carry[e] + rank;
-                const bool kept = sl < C;
-                slot[(t0 + t) * k + r] = kept ? sl : -1;
-                if (kept) atomicOr(&kept_l[(t * k + r) >> 5], 1u << ((t * k + r) & 31));
-            }
-            for (int q = tid; q < 16 * (kMaxExperts + 1); q += 1024) (&wcnt[buf ^ 1][0][0])[q] = 0;
-            lds_barrier();
-            if (tid < E) {
-                int sum = running[tid];
+            for (int w2 = 0; w2 < 16; ++w2) c[w2] = wcnt[r & 1][w2][lane];
 #pragma unroll
-                for (int w2 = 0; w2 < 16; ++w2) sum += wcnt[buf][w2][tid];
-                if (i + 1 < ntile) {
-                    running[tid] = sum;
-                } else {  // round done: its demand moves into the carry
-                    running[tid] = 0;
-                    total += sum;
-                    carry[tid] = min(C, total);
-                }
+            for (int w2 = 0; w2 < 16; ++w2) {
+                base += w2 < ws ? c[w2] : 0;
+                total += c[w2];
             }
         }
-    }
+#pragma unroll
+        for (int j = 0; j < KT; ++j) {
+            if (j >= nc) continue;
+            const int sl = __shfl(base, ex[j], 64) + rk[j];
+            if ((ch0 + j) * 64 + lane < Ng)
+                slot_l[tk[j] * k + r] = static_cast<uint16_t>(sl < C ? sl : kDropped);
+        }
     }
     if (tid < E) {
         counts[g * E + tid] = min(C, total);
@@ -1125,8 +1049,12 @@ __global__ __launch_bounds__(1024) void local_route_kernel(
     lds_barrier();
 #pragma unroll
     for (int u = 0; u < KA; ++u) {
+        if (u * 1024 >= nk) break;
         const int q = u * 1024 + tid;
-        if (q < nk) gate[t0 * k + q] = ((kept_l[q >> 5] >> (q & 31)) & 1u) ? pv[u] : 0.0f;
+        if (q >= nk) break;
+        const int sl = slot_l[q];
+        slot[t0 * k + q] = sl == kDropped ? -1 : sl;
+        gate[t0 * k + q] = sl == kDropped ? 0.0f : pv[u];
     }
 }
 
@@ -1186,8 +1114,9 @@ vmoe_status route_launch(const Dims& D, const void* x, const void* wr, const flo
                 f64_router_tokens(D.E));
         }
         if (local_route_fits(D)) {
-            auto kern = D.E <= 8 ? local_route_kernel<4>
-                      : D.E <= 16 ? local_route_kernel<8> : local_route_kernel<0>;
+            auto kern = D.E <= 8 ? local_route_kernel<3>
+                      : D.E <= 16 ? local_route_kernel<4>
+                      : D.E <= 32 ? local_route_kernel<5> : local_route_kernel<6>;
             kern<<<D.G, 1024, 0, st>>>(ws.keys, idx, probs, order, slot, gate, counts, row_base,
                                        D.G, D.Ng, D.E, D.k, D.C);
             if (D.G > 1) row_base_kernel<<<1, 1024, 0, st>>>(counts, row_base, D.G, D.E);

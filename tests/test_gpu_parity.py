@@ -109,6 +109,14 @@ ROUTE_CASES = [
     ("multi_block_two_groups", 2 * 9000, 8, 2, 2, dict(seed=18, scale=2.0)),
     ("multi_block_k4_three_groups", 3 * 5000, 16, 4, 3, dict(seed=19, scale=2.0)),
     ("multi_block_groups_equal_priorities", 2 * 8500, 4, 2, 2, dict(seed=20, tie_every=1)),
+    # one block per group: chunks of 64 order positions (whole, one more, one
+    # short; fewer chunks than waves), 5 and 6 expert bits, k = E at the limit
+    ("single_block_e20_k3", 1500, 20, 3, 1, dict(seed=21, scale=2.0)),
+    ("single_block_e32_chunk_edges", 5 * 65, 32, 2, 5, dict(seed=22, scale=2.0)),
+    ("single_block_e17_ties", 2 * 1023, 17, 2, 2, dict(seed=23, tie_every=3)),
+    ("single_block_e33_full_rows", 4 * 1024, 33, 4, 1, dict(seed=24, scale=2.0)),
+    ("single_block_one_token_groups", 6, 8, 2, 6, dict(seed=25)),
+    ("single_block_k_equals_e64", 256, 64, 64, 1, dict(seed=26, scale=1.5)),
 ]
 
 
