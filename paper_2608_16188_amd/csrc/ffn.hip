@@ -608,6 +608,15 @@ __device__ __forceinline__ void ring_barrier() {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
+// A barrier that waits for this wave's LDS accesses only: its stores stay in
+// flight across it.
+__device__ __forceinline__ void lds_barrier() {
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+
 // ds_read_b64_tr_b16: within each 16-lane group, lane j reads 4 bf16 at its
 // address and lane i receives element i % 4 of lanes i/4, i/4+4, i/4+8, i/4+12.
 // With lane j pointing at row j/4, column 4*(j%4) of a 4 x 16 block, lane i
@@ -1185,54 +1194,158 @@ __device__ __forceinline__ void light_tile(const GemmArgs& p, __amdgpu_buffer_rs
     gemm_epilogue<T, CFG, EPI>(p, acc, arrays.b0, ep, 0.0f, false, e, M, N, m0, n0w, sl == 0 ? 1 : 0);
 }
 
-// Epilogue of a phased tile: each wave turns its accumulators into outputs
-// strip by strip (64 rows x 32 columns of panel b; f32 outputs one 32-row
-// block at a time), through 4 KB of LDS of its own, 16-byte chunks XOR-swizzled
-// by row, to be stored as 64- (bf16) or 128-byte (f32) row segments. A wave's
-// LDS accesses run in order, so no pass needs a barrier, and the operand
-// stages are not touched. The saved gelu'(H) arrives in the same row segments,
-// all strips requested before the first is used.
+// Epilogue of a phased tile with bf16 outputs: each wave turns its accumulators
+// into outputs strip by strip (64 rows x 32 columns of panel b), through 4 KB of
+// LDS of its own, 16-byte chunks XOR-swizzled by row, to be stored as 64-byte row
+// segments. A wave's LDS accesses run in order, so no pass needs a barrier, and
+// the operand stages are not touched. The saved gelu'(H) arrives in the same row
+// segments, all strips requested before the first is used.
 template <class T, int EPI>
 __device__ __forceinline__ void phase_epilogue(const GemmArgs& p, f32x16 (&acc)[T::FM][T::PB],
-                                               float (&rsum)[T::FM], bool row_sum, uint16_t* stg,
-                                               int e, int M, int N, int m0, int n0,
+                                               uint16_t* stg, int e, int M, int N, int m0, int n0,
                                                int fm_live) {
+    static_assert(EPI != EPI_F32, "bf16 outputs");
     constexpr int PB = T::PB, FM = T::FM;
     const int lane = threadIdx.x & 63, wave = wave_id();
     const int wm = wave / T::WGN, wn = wave % T::WGN;
     const int mr = m0 + 64 * wm, nc = n0 + 32 * wn;  // the wave's first row and column
-    if constexpr (EPI == EPI_F32) {
-        if (row_sum) {
-#pragma unroll
-            for (int i = 0; i < FM; ++i) {
-                const float t = rsum[i] + __shfl_xor(rsum[i], 32, 64);
-                const int m = mr + 32 * i + lane;
-                if (lane < 32 && m < M) p.bsum[static_cast<size_t>(e) * M + m] = t;
-            }
-        }
-    }
     if (fm_live == 0) return;
-    typedef __attribute__((address_space(3))) uint16_t lds_u16;
-    typedef __attribute__((address_space(3))) v4i32 lds_v4;
     typedef int v2i32 __attribute__((ext_vector_type(2)));
     typedef __attribute__((address_space(3))) v2i32 lds_v2;
     lds_u16* const s = (lds_u16*)(stg) + wave * 2048;
     const size_t ebase = static_cast<size_t>(e) * p.out_estride;
-    if constexpr (EPI == EPI_F32) {
-        // row r of the staged block: 8 chunks of 16 bytes
+    // lane's row segment u of a strip: row 16 u + lane / 4, chunk lane % 4
+    const int sr = lane >> 2, sc = lane & 3;
+    auto slot = [&](int r, int c) { return s + r * 32 + ((c ^ ((r >> 2) & 3)) << 3); };
+    v4i32 aux[EPI == EPI_GELU_GRAD ? PB : 1][4];
+    if constexpr (EPI == EPI_GELU_GRAD) {
+#pragma unroll
+        for (int b = 0; b < PB; ++b)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int m = mr + 16 * u + sr, n = nc + 64 * b + 8 * sc;
+                aux[b][u] = (m < M && n < N)
+                                ? *reinterpret_cast<const v4i32*>(
+                                      static_cast<const uint16_t*>(p.aux) + ebase +
+                                      static_cast<size_t>(m) * p.ldo + n)
+                                : v4i32{0, 0, 0, 0};
+            }
+    }
+    // the staged strip to `dst` as row segments
+    auto rows_out = [&](int b, void* dst) {
+        const int n = nc + 64 * b + 8 * sc;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int m = mr + 16 * u + sr;
+            const v4i32 v = *reinterpret_cast<lds_v4*>(slot(16 * u + sr, sc));
+            if (m < M && n < N)
+                *reinterpret_cast<v4i32*>(static_cast<uint16_t*>(dst) + ebase +
+                                          static_cast<size_t>(m) * p.ldo + n) = v;
+        }
+    };
+#pragma unroll
+    for (int b = 0; b < PB; ++b) {
+        uint2 dg[EPI == EPI_FWD1 ? FM : 1][4];
+        if constexpr (EPI == EPI_GELU_GRAD) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                *reinterpret_cast<lds_v4*>(slot(16 * u + sr, sc)) = aux[b][u];
+        }
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float r[4] = {acc[i][b][4 * q], acc[i][b][4 * q + 1], acc[i][b][4 * q + 2],
+                              acc[i][b][4 * q + 3]};
+                lds_u16* const at = slot(32 * i + (lane & 31), q) + 4 * (lane >> 5);
+                if constexpr (EPI == EPI_GELU_GRAD) {
+                    const v2i32 gg = *reinterpret_cast<lds_v2*>(at);
+                    r[0] *= bf16_to_f32(gg[0] & 0xFFFFu);
+                    r[1] *= __uint_as_float(gg[0] & 0xFFFF0000u);
+                    r[2] *= bf16_to_f32(gg[1] & 0xFFFFu);
+                    r[3] *= __uint_as_float(gg[1] & 0xFFFF0000u);
+                }
+                if constexpr (EPI == EPI_FWD1) {
+                    float g[4], d[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) gelu_pair(r[c], g[c], d[c]);
+                    dg[i][q] = make_uint2(pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3]));
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) r[c] = g[c];
+                }
+                *reinterpret_cast<lds_v2*>(at) =
+                    v2i32{static_cast<int>(pack_bf16x2(r[0], r[1])),
+                          static_cast<int>(pack_bf16x2(r[2], r[3]))};
+            }
+        rows_out(b, p.out);
+        if constexpr (EPI == EPI_FWD1) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<lds_v2*>(slot(32 * i + (lane & 31), q) +
+                                               4 * (lane >> 5)) =
+                        v2i32{static_cast<int>(dg[i][q].x), static_cast<int>(dg[i][q].y)};
+            rows_out(b, p.out2);
+        }
+    }
+}
+
+// Epilogue of a phased weight-gradient tile. Where rows are whole 128-byte lines,
+// strip by strip as above: a 32-row block's 32 columns of a panel, one line a row,
+// without a barrier. Elsewhere such strips write every line in two parts, so whole
+// rows of the tile go out instead, a row an instruction: in pass i every wave puts
+// its 32-row block i of all panels into the tile's arrays, whose operands are done
+// with (16 rows to a 16 KB piece), and wave w stores the 16 rows of piece w.
+// Measured, expert MLP backward with strips / whole rows: 8 rows an expert, E = 64,
+// d = 1000, f = 2000 454 / 335 us (365 with the former 256-byte segments of a wave);
+// 30 rows, E = 64, d = 520, f = 2088 329 / 244 (255); 64 rows, E = 32, d = 1024,
+// f = 4096 (whole lines) 337 / 341 (385); 768 x 3072 207 / 213 (229).
+template <class T>
+__device__ __forceinline__ void phase_epilogue_f32(const GemmArgs& p,
+                                                   f32x16 (&acc)[T::FM][T::PB],
+                                                   float (&rsum)[T::FM], bool row_sum,
+                                                   const LdsArrays& arrays, int e, int M, int N,
+                                                   int m0, int n0, int fm_live) {
+    constexpr int PB = T::PB, FM = T::FM, ROW = 128 * PB;  // a staged row, in 16-bit words
+    const int lane = threadIdx.x & 63, wave = wave_id();
+    const int wm = wave / T::WGN, wn = wave % T::WGN;
+    const int mr = m0 + 64 * wm;
+    if (row_sum) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            const float t = rsum[i] + __shfl_xor(rsum[i], 32, 64);
+            const int m = mr + 32 * i + lane;
+            if (lane < 32 && m < M) p.bsum[static_cast<size_t>(e) * M + m] = t;
+        }
+    }
+    float* const out = static_cast<float*>(p.out) + static_cast<size_t>(e) * p.out_estride;
+    // chunk q (4 columns) of the lane's row in block i, panel b
+    auto chunk = [&](int i, int b, int q) {
+        return __builtin_bit_cast(v4i32, make_float4(acc[i][b][4 * q], acc[i][b][4 * q + 1],
+                                                     acc[i][b][4 * q + 2], acc[i][b][4 * q + 3]));
+    };
+    // weight gradients are not read again by the layer: streaming stores keep
+    // them from displacing cached activations
+    auto store = [&](v4i32 v, int m, int n) {
+        __builtin_nontemporal_store(
+            v, reinterpret_cast<v4i32*>(out + static_cast<size_t>(m) * p.ldo + n));
+    };
+    if (p.ldo % 32 == 0) {
+        if (fm_live == 0) return;
+        lds_u16* const s = (lds_u16*)(arrays.b6) + wave * 2048;
+        const int nc = n0 + 32 * wn;
 #pragma unroll
         for (int i = 0; i < FM; ++i) {
             if (i >= fm_live) break;
 #pragma unroll
             for (int b = 0; b < PB; ++b) {
+                // row r of the staged block: 8 chunks of 16 bytes
                 const int r = lane & 31;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int c = 2 * q + (lane >> 5);
-                    const float4 v = make_float4(acc[i][b][4 * q], acc[i][b][4 * q + 1],
-                                                 acc[i][b][4 * q + 2], acc[i][b][4 * q + 3]);
-                    *reinterpret_cast<lds_v4*>(s + r * 64 + ((c ^ (r & 7)) << 3)) =
-                        __builtin_bit_cast(v4i32, v);
+                    *reinterpret_cast<lds_v4*>(s + r * 64 + ((c ^ (r & 7)) << 3)) = chunk(i, b, q);
                 }
                 const int n = nc + 64 * b + 4 * (lane & 7);
 #pragma unroll
@@ -1240,89 +1353,36 @@ __device__ __forceinline__ void phase_epilogue(const GemmArgs& p, f32x16 (&acc)[
                     const int rr = 8 * u + (lane >> 3), m = mr + 32 * i + rr;
                     const v4i32 v = *reinterpret_cast<lds_v4*>(
                         s + rr * 64 + (((lane & 7) ^ (rr & 7)) << 3));
-                    // weight gradients are not read again by the layer: streaming
-                    // stores keep them from displacing cached activations
-                    if (m < M && n < N)
-                        __builtin_nontemporal_store(
-                            v, reinterpret_cast<v4i32*>(static_cast<float*>(p.out) + ebase +
-                                                        static_cast<size_t>(m) * p.ldo + n));
+                    if (m < M && n < N) store(v, m, n);
                 }
             }
         }
-    } else {
-        // lane's row segment u of a strip: row 16 u + lane / 4, chunk lane % 4
-        const int sr = lane >> 2, sc = lane & 3;
-        auto slot = [&](int r, int c) { return s + r * 32 + ((c ^ ((r >> 2) & 3)) << 3); };
-        v4i32 aux[EPI == EPI_GELU_GRAD ? PB : 1][4];
-        if constexpr (EPI == EPI_GELU_GRAD) {
+        return;
+    }
+    lds_u16* const lo = pick_lds<8>(2 * wm, arrays);
+    lds_u16* const hi = pick_lds<8>(2 * wm + 1, arrays);
+    lds_u16* const mine = pick_lds<8>(wave, arrays);
+    const int r = lane & 15, n = n0 + 4 * lane;
+    lds_u16* const put = ((lane & 16) ? hi : lo) + r * ROW;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+        lds_barrier();  // the operands, or the previous pass's rows, are read
+        if (i < fm_live) {
 #pragma unroll
             for (int b = 0; b < PB; ++b)
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int m = mr + 16 * u + sr, n = nc + 64 * b + 8 * sc;
-                    aux[b][u] = (m < M && n < N)
-                                    ? *reinterpret_cast<const v4i32*>(
-                                          static_cast<const uint16_t*>(p.aux) + ebase +
-                                          static_cast<size_t>(m) * p.ldo + n)
-                                    : v4i32{0, 0, 0, 0};
+                for (int q = 0; q < 4; ++q) {
+                    const int c = 16 * b + 8 * wn + 2 * q + (lane >> 5);
+                    *reinterpret_cast<lds_v4*>(put + ((c ^ r) << 3)) = chunk(i, b, q);
                 }
         }
-        // the staged strip to `dst` as row segments
-        auto rows_out = [&](int b, void* dst) {
-            const int n = nc + 64 * b + 8 * sc;
+        lds_barrier();
+        const int m1 = mr + 32 * i + 16 * wn;  // the wave's first row
+        if (lane < 16 * PB && n < N) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int m = mr + 16 * u + sr;
-                const v4i32 v = *reinterpret_cast<lds_v4*>(slot(16 * u + sr, sc));
-                if (m < M && n < N)
-                    *reinterpret_cast<v4i32*>(static_cast<uint16_t*>(dst) + ebase +
-                                              static_cast<size_t>(m) * p.ldo + n) = v;
-            }
-        };
-#pragma unroll
-        for (int b = 0; b < PB; ++b) {
-            uint2 dg[EPI == EPI_FWD1 ? FM : 1][4];
-            if constexpr (EPI == EPI_GELU_GRAD) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    *reinterpret_cast<lds_v4*>(slot(16 * u + sr, sc)) = aux[b][u];
-            }
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float r[4] = {acc[i][b][4 * q], acc[i][b][4 * q + 1], acc[i][b][4 * q + 2],
-                                  acc[i][b][4 * q + 3]};
-                    lds_u16* const at = slot(32 * i + (lane & 31), q) + 4 * (lane >> 5);
-                    if constexpr (EPI == EPI_GELU_GRAD) {
-                        const v2i32 gg = *reinterpret_cast<lds_v2*>(at);
-                        r[0] *= bf16_to_f32(gg[0] & 0xFFFFu);
-                        r[1] *= __uint_as_float(gg[0] & 0xFFFF0000u);
-                        r[2] *= bf16_to_f32(gg[1] & 0xFFFFu);
-                        r[3] *= __uint_as_float(gg[1] & 0xFFFF0000u);
-                    }
-                    if constexpr (EPI == EPI_FWD1) {
-                        float g[4], d[4];
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) gelu_pair(r[c], g[c], d[c]);
-                        dg[i][q] = make_uint2(pack_bf16x2(d[0], d[1]), pack_bf16x2(d[2], d[3]));
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) r[c] = g[c];
-                    }
-                    *reinterpret_cast<lds_v2*>(at) =
-                        v2i32{static_cast<int>(pack_bf16x2(r[0], r[1])),
-                              static_cast<int>(pack_bf16x2(r[2], r[3]))};
-                }
-            rows_out(b, p.out);
-            if constexpr (EPI == EPI_FWD1) {
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *reinterpret_cast<lds_v2*>(slot(32 * i + (lane & 31), q) +
-                                                   4 * (lane >> 5)) =
-                            v2i32{static_cast<int>(dg[i][q].x), static_cast<int>(dg[i][q].y)};
-                rows_out(b, p.out2);
+            for (int u = 0; u < 16; ++u) {
+                const v4i32 v = *reinterpret_cast<lds_v4*>(mine + u * ROW + ((lane ^ u) << 3));
+                if (m1 + u < M) store(v, m1 + u, n);
             }
         }
     }
@@ -1609,7 +1669,11 @@ __device__ __forceinline__ void phase_tile(const GemmArgs& p, __amdgpu_buffer_rs
     else ring(std::integral_constant<int, 0>{});
     // the requests past K have landed (here, so that no wait stands behind the stores)
     __builtin_amdgcn_s_waitcnt(VmWait<0>::imm | (15 << 8));
-    phase_epilogue<T, EPI>(p, acc, rsum, row_sum, stg, e, M, N, m0, n0, fm_live);
+    if constexpr (EPI == EPI_F32)
+        phase_epilogue_f32<T>(p, acc, rsum, row_sum, LdsArrays{a0, a1, bl0, bh0, bl1, bh1, stg}, e, M,
+                              N, m0, n0, fm_live);
+    else
+        phase_epilogue<T, EPI>(p, acc, stg, e, M, N, m0, n0, fm_live);
 }
 
 // One BM x BN output tile of expert e per block of WGM x WGN waves, each
@@ -2105,10 +2169,7 @@ void gemm_bf16_kernel(GemmBatch batch) {
     // the next tile's first stages land in the buffers this epilogue staged
     // its outputs in: every wave's LDS accesses are done before any issues
     // them (its output stores stay in flight)
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    lds_barrier();
     }
 }
 
@@ -2534,6 +2595,10 @@ using TileBig = PhaseTile<4>;
 using TileNarrow = PhaseTile<3>;
 using TileSmall = Tile<128, 128, 2, 2, 32, 4, STAGE_DMA>;
 
+// Relative cost per tile area of the other tilings (256 x 256 is 1).
+constexpr double kNarrowCost = 1.05;
+constexpr double kSmallCost = 1.15;
+
 // Work of a launch in units of one CU's time: rounds of one-block-per-CU
 // waves times the tile's area (relative cost per tile area `eff`).
 double tile_cost(long long tiles, int bm, int bn, double eff) {
@@ -2574,7 +2639,7 @@ void launch_gemm(const Dims& D, const GemmArgs& a, int grid_m_rows, int sched, h
             // 101 -> 107 us there at ViT-B/16, 133 -> 141 on the 17-task batch)
             const long long tm = cdiv(grid_m_rows, 256);
             const double big = tile_cost(D.E * tm * cdiv(a.N, 256), 256, 256, 1.0);
-            const double narrow = tile_cost(D.E * tm * cdiv(a.N, 192), 256, 192, 1.05);
+            const double narrow = tile_cost(D.E * tm * cdiv(a.N, 192), 256, 192, kNarrowCost);
             if (narrow < big)
                 launch_bf16<TileNarrow, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
             else
@@ -2801,8 +2866,8 @@ vmoe_status ffn_bwd_launch(const Dims& D, const void* xe, const int32_t* counts,
             return D.E * (static_cast<long long>(cdiv(D.d, bm)) * cdiv(D.f, bn) +
                           static_cast<long long>(cdiv(D.f, bm)) * cdiv(D.d, bn));
         };
-        const double small = tile_cost((tiles(128, 128) + 1) / 2, 256, 128, 1.15);
-        const double narrow = tile_cost(tiles(256, 192), 256, 192, 1.05);
+        const double small = tile_cost((tiles(128, 128) + 1) / 2, 256, 128, kSmallCost);
+        const double narrow = tile_cost(tiles(256, 192), 256, 192, kNarrowCost);
         const double big = tile_cost(tiles(256, 256), 256, 256, 1.0);
         // (the gathered input-weight gradient takes the same tiling, so its
         // results, bias-gradient sums included, are the unfused call's bits)

@@ -2,6 +2,8 @@
 from __future__ import annotations
 
 import functools
+import os
+import re
 import sys
 
 import numpy as np
@@ -12,6 +14,43 @@ from paper_2608_16188_amd import workloads as W
 # Tolerance on max|gpu - oracle| / max|oracle| per tensor: bf16 storage with
 # f32 accumulation vs f32 end to end.
 TOL = {W.F32: 1e-4, W.BF16: 2e-2}
+
+
+@functools.lru_cache(maxsize=1)
+def _tile_costs():
+    """(256 x 192, 128 x 128): the bf16 tilings' relative costs, from ffn.hip."""
+    src = os.path.join(os.path.dirname(W.__file__), "csrc", "ffn.hip")
+    with open(src) as f:
+        text = f.read()
+    return tuple(float(re.search(rf"constexpr double {n} = ([0-9.]+);", text).group(1))
+                 for n in ("kNarrowCost", "kSmallCost"))
+
+
+def _rounds(tiles, bm, bn, cost):
+    return -(-tiles // 256) * bm * bn * cost
+
+
+def weight_grad_tile(d, f, E):
+    """Tiling of the bf16 weight gradients: 'big' (256 x 256), 'narrow' (256 x
+    192) or 'small' (128 x 128), by the library's rule."""
+    narrow_cost, small_cost = _tile_costs()
+
+    def tiles(bm, bn):
+        return E * (-(-d // bm) * -(-f // bn) + -(-f // bm) * -(-d // bn))
+
+    small = _rounds((tiles(128, 128) + 1) // 2, 256, 128, small_cost)
+    narrow = _rounds(tiles(256, 192), 256, 192, narrow_cost)
+    big = _rounds(tiles(256, 256), 256, 256, 1.0)
+    if narrow <= small and narrow <= big:
+        return "narrow"
+    return "big" if big <= small else "small"
+
+
+def row_tile(rows, d, E):
+    """Tiling of the d-wide bf16 row products of buffers of `rows` rows."""
+    tm = -(-rows // 256)
+    narrow = _rounds(E * tm * -(-d // 192), 256, 192, _tile_costs()[0])
+    return "narrow" if narrow < _rounds(E * tm * -(-d // 256), 256, 256, 1.0) else "big"
 
 
 def say(*a):

@@ -2,7 +2,10 @@
 
 Row counts around the 32-row matrix-core blocks, the waves' 64- and 128-row
 shares and the 256-row tiles, widths that end inside a 64-deep stage and inside
-a tile's columns, experts without rows. Every product is compared on its own
+a tile's columns, experts without rows. The first cases' weight gradients take
+the 128 x 128 tiling and their d-wide row products the 256 x 192 one; WEIGHT_CASES
+and ROW_CASES name the tiling they are there for and check it against the
+library's rule. Every product is compared on its own
 with a float64 product of the same bf16 operands (the backward's and the
 down-projection's operands are the GPU's own earlier outputs), and rows past an
 expert's count hold NaN on input and must stay as they were on output.
@@ -21,7 +24,7 @@ import torch
 
 from paper_2608_16188_amd import vmoe as V
 
-from .gpu_common import say
+from .gpu_common import row_tile, say, weight_grad_tile
 
 pytestmark = pytest.mark.gpu
 
@@ -48,6 +51,28 @@ CASES = [
 ]
 # 16 and more experts: dxe beside the weight gradients
 MANY = (200, 520, [0, 1, 7, 32, 33, 34, 63, 64, 65, 100, 127, 128, 129, 200, 255, 256, 257])
+# weight gradients on the 256-row tiles, rows being k here: none, one, a stage of
+# 64 and its neighbours, an odd number of stages; (tiling, d, f, rows, quota
+# scheduling). 544, 1056 and 160 make rows of whole 128-byte lines, 520, 1032 and
+# 136 of split ones
+_K = [0, 1, 31, 33, 63, 64, 65, 128, 129, 257, 192, 2]
+WEIGHT_CASES = [
+    ("big", 520, 1032, [0, 1, 33, 64, 65, 129, 257, 31], False),
+    ("big", 520, 1032, [63, 128, 0, 2, 192, 64, 1, 130], True),
+    ("big", 544, 1056, [0, 1, 33, 64, 65, 129, 257, 31], False),
+    ("big", 520, 1056, [63, 128, 0, 2, 192, 64, 1, 130], False),
+    ("narrow", 136, 520, [_K[e % 12] for e in range(64)], False),
+    ("narrow", 136, 520, [_K[e * 5 % 12] for e in range(64)], True),
+    ("narrow", 160, 544, [_K[e * 7 % 12] for e in range(64)], False),
+]
+# d-wide row products on 256 x 256 tiles, buffers of one, two and four m-tiles
+# (light experts in one, two and four column parts): (tiling, d, f, rows, quota)
+ROW_CASES = [
+    ("big", 1000, 64, [(17 * e + 1) % 257 for e in range(64)], False),
+    ("big", 1000, 64, [500, 257] + [(11 * e) % 40 for e in range(30)], False),
+    ("big", 1000, 72, [800, 0, 1, 31, 32, 33, 64, 257, 512, 513, 769, 16, 65, 255, 256, 20], False),
+    ("big", 1000, 72, [800, 0, 1, 31, 32, 33, 64, 257, 512, 513, 769, 16, 65, 255, 256, 20], True),
+]
 # f32 layers: k shares of no, one and an odd number of 8-deep runs, tiles of 32
 # and (enough of them in a launch) of 64
 F32_CASES = [
@@ -94,8 +119,24 @@ def test_f32_products_at_tile_edges(d, f, rows):
     _products(d, f, rows, torch.float32)
 
 
-def _products(d, f, rows, dt):
-    say("ffn edges", d, f, rows, dt)
+@pytest.mark.parametrize("tile,d,f,rows,quota", WEIGHT_CASES,
+                         ids=lambda v: "" if isinstance(v, list) else str(v))
+def test_weight_gradients_at_tile_edges(tile, d, f, rows, quota):
+    assert weight_grad_tile(d, f, len(rows)) == tile
+    _products(d, f, rows, torch.bfloat16, quota)
+
+
+@pytest.mark.parametrize("tile,d,f,rows,quota", ROW_CASES,
+                         ids=lambda v: "" if isinstance(v, list) else str(v))
+def test_row_products_at_tile_edges(tile, d, f, rows, quota):
+    assert row_tile(max(rows), d, len(rows)) == tile
+    _products(d, f, rows, torch.bfloat16, quota)
+
+
+def _products(d, f, rows, dt, quota=False):
+    say("ffn edges", d, f, rows, dt, quota)
+    fwd = V.vmoe_expert_ffn_fwd_quota if quota else V.vmoe_expert_ffn_fwd
+    bwd = V.vmoe_expert_ffn_bwd_quota if quota else V.vmoe_expert_ffn_bwd
 
     def _stored(ref, bound):  # a stored result: rounded once more in bf16
         return _rounded(ref, bound) if dt == torch.bfloat16 else bound
@@ -123,12 +164,11 @@ def _products(d, f, rows, dt):
         return torch.full(shape, 77.0, dtype=dtype, device="cuda")
 
     act, act_grad, ye = out(E, R, f), out(E, R, f), out(E, R, d)
-    V.vmoe_expert_ffn_fwd(s, xe, counts, w1, b1, w2, b2, act, act_grad, ye)
+    fwd(s, xe, counts, w1, b1, w2, b2, act, act_grad, ye)
     dh, dxe = out(E, R, f), out(E, R, d)
     g = {n: out(*sh, dtype=torch.float32) for n, sh in
          dict(dw1=(E, f, d), db1=(E, f), dw2=(E, d, f), db2=(E, d)).items()}
-    V.vmoe_expert_ffn_bwd(s, xe, counts, w1, w2, act, act_grad, dye, dh, dxe, g["dw1"], g["db1"],
-                          g["dw2"], g["db2"])
+    bwd(s, xe, counts, w1, w2, act, act_grad, dye, dh, dxe, g["dw1"], g["db1"], g["dw2"], g["db2"])
     torch.cuda.synchronize()
 
     c = {n: t.double().cpu() for n, t in dict(xe=xe, dye=dye, w1=w1, w2=w2, b1=b1, b2=b2, act=act,

@@ -13,7 +13,7 @@ import torch
 from paper_2608_16188_amd import workloads as W
 from paper_2608_16188_amd.layer import LayerBuffers
 
-from .gpu_common import say, workload_inputs
+from .gpu_common import say, weight_grad_tile, workload_inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -40,6 +40,11 @@ CASES = [
                     k=2, capacity_factor=1.0, hot_experts=2, hot_offset=0.8),
     W.custom_config("bf16_small_batch_g", n_tokens=100, d_model=136, d_ff=520, n_experts=4, k=2,
                     capacity_factor=1.05, router_std=0.2),
+    # weight gradients on 256 x 256 and 256 x 192 tiles
+    W.custom_config("bf16_big_tiles_g", n_tokens=512, d_model=520, d_ff=1032, n_experts=8, k=2,
+                    capacity_factor=1.25, router_std=0.2),
+    W.custom_config("bf16_narrow_tiles_g", n_tokens=1500, d_model=136, d_ff=520, n_experts=64,
+                    k=2, capacity_factor=1.5, router_std=0.3),
 ]
 OUTS = ("a", "a_grad", "ye", "y", "dye", "dgate", "dh", "dxe", "dw1", "db1", "dw2", "db2", "dx",
         "dw_router")
@@ -57,6 +62,8 @@ def test_gathered_step_bit_identical(case):
         cfg, inp = workload_inputs(case)
     else:
         cfg, inp = case, W.make_inputs(case)
+    if "_tiles" in cfg.name:
+        assert weight_grad_tile(cfg.d_model, cfg.d_ff, cfg.n_experts) in cfg.name
     say("gathered vs unfused step", cfg.name)
     L = LayerBuffers(cfg, inp)
     L.step()

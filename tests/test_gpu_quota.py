@@ -20,7 +20,7 @@ from paper_2608_16188_amd import vmoe as V
 from paper_2608_16188_amd import workloads as W
 from paper_2608_16188_amd.layer import LayerBuffers
 
-from .gpu_common import say, workload_inputs
+from .gpu_common import say, weight_grad_tile, workload_inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -93,6 +93,11 @@ QUOTA_SMALL = [
                     capacity_factor=1.0, router_std=0.05),
     W.custom_config("bf16_light_tails_q", n_tokens=2240, d_model=200, d_ff=520, n_experts=16,
                     k=2, capacity_factor=1.0, hot_experts=2, hot_offset=0.8),
+    # weight gradients on 256 x 256 and 256 x 192 tiles
+    W.custom_config("bf16_big_tiles_q", n_tokens=512, d_model=520, d_ff=1032, n_experts=8, k=2,
+                    capacity_factor=1.25, router_std=0.2),
+    W.custom_config("bf16_narrow_tiles_q", n_tokens=1500, d_model=136, d_ff=520, n_experts=64,
+                    k=2, capacity_factor=1.5, router_std=0.3),
 ]
 OUTS = ("a", "a_grad", "ye", "y", "dye", "dgate", "dh", "dxe", "dw1", "db1", "dw2", "db2", "dx")
 
@@ -109,6 +114,8 @@ def test_quota_schedule_bit_identical(case):
         cfg, inp = workload_inputs(case)
     else:
         cfg, inp = case, W.make_inputs(case)
+    if "_tiles" in cfg.name:
+        assert weight_grad_tile(cfg.d_model, cfg.d_ff, cfg.n_experts) in cfg.name
     say("quota vs default schedule", cfg.name)
     L = LayerBuffers(cfg, inp)
     L.step()
