@@ -599,12 +599,15 @@ struct VmWait {
     static constexpr int imm = (N & 15) | ((N >> 4) << 14) | (7 << 4);
 };
 
-// Workgroup barrier for the stage ring. __syncthreads() fences all memory at
+// Workgroup barrier for the operand stages. __syncthreads() fences all memory at
 // workgroup scope, which waits for every LDS DMA in flight (vmcnt(0)) and
-// would cap the prefetch at one stage; here the caller's s_waitcnt has
-// already retired this wave's LDS reads and the DMA of the stage about to be
-// read, so a bare s_barrier suffices. The signal fences keep the compiler
-// from moving memory accesses across it.
+// would cap the prefetch at one stage, so the callers see to two things
+// themselves: the DMA of what is read next has landed (their s_waitcnt on vmcnt),
+// and this wave's reads of what is refilled next are done. The ring of whole
+// stages waits for the latter too (lgkmcnt(0) in VmWait). phase_tile does not: it
+// refills a panel, or a stage's A, one phase after the phase whose products
+// consumed the fragments read from it, and consuming them waited for those reads.
+// The signal fences keep the compiler from moving memory accesses across it.
 __device__ __forceinline__ void ring_barrier() {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_barrier();
@@ -1416,8 +1419,12 @@ __device__ __forceinline__ void phase_epilogue_f32(const GemmArgs& p,
 //   phase 0: panel PB - 1 of stage kt + 1     phase 1: panel 0, A of stage kt + 2
 //   phase b: panel b - 1 of stage kt + 2
 // and waits before phase b for what phase b reads, counting what was issued
-// after it. Fragments read in a phase are used in the next, so the barrier
-// that opens the phase after that needs no wait for LDS reads.
+// after it. Every fragment read in a phase is used by the next phase's products
+// (the last phase's A fragments by all of them in the next stage's phase 0), which
+// the scheduling barriers keep ahead of the barrier that opens the phase after
+// that: there alone may their LDS be refilled, without a wait for LDS reads.
+// Only the last stage's read of a stage past K goes unused; nothing is requested
+// after it. (A wave without live rows reads no fragments and only requests.)
 template <int PB>
 struct PhaseWaits {
     static constexpr int issued(int b) { return b == 1 ? 5 : 1; }  // wave instructions, phase b
@@ -1597,8 +1604,6 @@ __device__ __forceinline__ void phase_tile(const GemmArgs& p, __amdgpu_buffer_rs
         auto stage = [&](int kt, uint16_t* ac, uint16_t* an, auto parity, auto inside) {
             constexpr int S = decltype(parity)::value;
             using NX = std::integral_constant<int, 1 - S>;
-            constexpr bool IN = decltype(inside)::value;
-            const bool live = IN || kt < nk;  // uniform
             auto phase = [&](auto which) {
                 constexpr int b = decltype(which)::value;
                 constexpr int cur = (S * PB + b) & 1;
@@ -1606,14 +1611,10 @@ __device__ __forceinline__ void phase_tile(const GemmArgs& p, __amdgpu_buffer_rs
                 ring_barrier();
                 const uint16_t* bs = b < PB - 1 ? panel(parity, b + 1) : panel(NX{}, 0);
                 auto products = [&](int ks) {
-                    if constexpr (FL > 0) {
-                        if (live) {
 #pragma unroll
-                            for (int i = 0; i < FL; ++i)
-                                acc[i][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                                    fb[cur][ks], fa[i][ks], acc[i][b], 0, 0, 0);
-                        }
-                    }
+                    for (int i = 0; i < FL; ++i)
+                        acc[i][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            fb[cur][ks], fa[i][ks], acc[i][b], 0, 0, 0);
                 };
                 auto next_b = [&](int ks) {
                     if constexpr (FL > 0)
@@ -1662,9 +1663,12 @@ __device__ __forceinline__ void phase_tile(const GemmArgs& p, __amdgpu_buffer_rs
             stage(kt, a0, a1, P0{}, YES{});
             stage(kt + 1, a1, a0, P1{}, YES{});
         }
+        // (an odd last stage runs alone: with a stage of zeros after it an expert of
+        // at most 64 rows paid for two stages of weight gradients, backward at 64
+        // rows, E = 64, d = 1008, f = 2016 358 us against 339)
         for (; kt < nk; kt += 2) {
             stage(kt, a0, a1, P0{}, NO{});
-            stage(kt + 1, a1, a0, P1{}, NO{});
+            if (kt + 1 < nk) stage(kt + 1, a1, a0, P1{}, NO{});
         }
     };
     if (fm_live > 1) ring(std::integral_constant<int, 2>{});
