@@ -2602,9 +2602,16 @@ using TileBig = PhaseTile<4>;
 using TileNarrow = PhaseTile<3>;
 using TileSmall = Tile<128, 128, 2, 2, 32, 4, STAGE_DMA>;
 
-// Relative cost per tile area of the other tilings (256 x 256 is 1).
+// Relative cost per tile area of the other tilings (256 x 256 is 1): of the
+// factors 1.0 to 1.6 for 128 x 128 and 1.0 to 1.15 for 256 x 192, those whose choice
+// came closest to the fastest tiling of each of 313 expert MLP backwards (d = 192
+// to 1024, f = 2 d to 4 d, E = 4 to 64, 16 to 1000 rows): 1.4 % above it in the mean.
+// (1.15 for 128 x 128, from the time before the 256-row tiles were phased, was
+// 3.3 % above it: 1000 rows, E = 32, d = 776, f = 3104 1061 us against 864, the
+// 128 x 128 tiles also holding up dxe beside them; 150 rows, E = 24, d = 384,
+// f = 1536 89 against 71.)
 constexpr double kNarrowCost = 1.05;
-constexpr double kSmallCost = 1.15;
+constexpr double kSmallCost = 1.3;
 
 // Work of a launch in units of one CU's time: rounds of one-block-per-CU
 // waves times the tile's area (relative cost per tile area `eff`).
@@ -2641,9 +2648,10 @@ void launch_gemm(const Dims& D, const GemmArgs& a, int grid_m_rows, int sched, h
             launch_bf16<TileSmall, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
         } else if constexpr (EPI == EPI_BIAS || EPI == EPI_STORE) {
             // Narrow outputs (N = d_model) give few tiles: 192-column tiles fill
-            // more CUs when that saves a round (a few per cent slower per area;
-            // the f-wide outputs have tiles enough, and 256 x 192 measured
-            // 101 -> 107 us there at ViT-B/16, 133 -> 141 on the 17-task batch)
+            // more CUs when that saves a round. (The f-wide outputs have tiles
+            // enough; with 256 x 192 there too the ViT-B/16 expert MLP forward
+            // took 162 -> 168 us, the 17-task step 1211 -> 1231, eight ViT-L/16
+            // images 294 -> 311.)
             const long long tm = cdiv(grid_m_rows, 256);
             const double big = tile_cost(D.E * tm * cdiv(a.N, 256), 256, 256, 1.0);
             const double narrow = tile_cost(D.E * tm * cdiv(a.N, 192), 256, 192, kNarrowCost);
@@ -2866,7 +2874,7 @@ vmoe_status ffn_bwd_launch(const Dims& D, const void* xe, const int32_t* counts,
     if (D.dtype == VMOE_BF16) {
         // both weight gradients in one launch (same kernel, independent tiles),
         // with the tiling of the least cost in rounds x tile area (128 x 128
-        // tiles run two per CU and cost a little more per flop)
+        // tiles run two per CU and cost more per flop)
         const GemmArgs both[2] = {w, v};
         const int rows_m[2] = {D.d, D.f};
         auto tiles = [&](int bm, int bn) {
