@@ -83,6 +83,13 @@ F32_CASES = [
     (72, 3080, [512, 500, 449, 0, 64, 65, 480, 1]),
     (3080, 40, [512, 500, 449, 0, 64, 65, 480, 1]),
 ]
+# f32, twelve and more 64 x 64 tiles a CU in the up-projection: k = d up to 224 (waves side by
+# side), and just above
+F32_MANY_TILES = [
+    (40, 328, [2049, 0, 1, 63, 64, 65, 2000, 300] * 2),
+    (224, 520, [1473, 0, 33, 64, 1408, 127, 128, 129] * 2),
+    (232, 520, [1473, 0, 33, 64, 1408, 127, 128, 129] * 2),
+]
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -114,7 +121,7 @@ def test_products_at_tile_edges(d, f, rows):
     _products(d, f, rows, torch.bfloat16)
 
 
-@pytest.mark.parametrize("d,f,rows", F32_CASES, ids=lambda v: str(v) if isinstance(v, int) else "")
+@pytest.mark.parametrize("d,f,rows", F32_CASES + F32_MANY_TILES, ids=lambda v: str(v) if isinstance(v, int) else "")
 def test_f32_products_at_tile_edges(d, f, rows):
     _products(d, f, rows, torch.float32)
 
