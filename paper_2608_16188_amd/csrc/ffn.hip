@@ -4,8 +4,8 @@
 // one output tile of one expert per block. The tiles of nearly every launch
 // are 256 x 256 or 256 x 192 (PhaseTile<>, phase_tile: eight waves, one block
 // per CU, 64-deep stages taken in 64-column phases); small weight gradients
-// take 128 x 128 with four waves on a plain ring of stages (Tile<>, two blocks
-// per CU). A wave accumulates its sub-tile with v_mfma_f32_32x32x16_bf16 in
+// take 128 x 128 with four waves on a plain ring of stages (SmallTile, ring_tile,
+// two blocks per CU). A wave accumulates its sub-tile with v_mfma_f32_32x32x16_bf16 in
 // f32. Operands reach LDS through buffer loads that write LDS directly (16
 // bytes per lane, out-of-range offsets read as zero, so ragged tails need no
 // branch); later stages' loads stay in flight across the barriers (partial
@@ -367,18 +367,13 @@ __device__ __forceinline__ int wave_id() {
     return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
 }
 
-// Two ways of staging a KB-deep operand tile (KB = 32 or 64) in LDS:
-//   STAGE_REG: global -> registers -> ds_write, rows padded (k-major rows of
-//              KB + 8 bf16, mn-major rows of ROWS + 32 bf16), two stages;
-//   STAGE_DMA: buffer_load ... lds straight into LDS (no registers, so a ring
-//              of NS stages costs LDS only): lane L of a wave instruction fills
-//              bytes [16 L, 16 L + 16) of a 1 KB block, so rows are unpadded and
-//              16-byte chunks are XOR-swizzled instead (k-major: chunk ^ ((row / P)
-//              mod Q) with P rows per 256 bytes and Q chunks per row; mn-major:
-//              chunk ^ s (k mod 4) with s = 4, or 2 when a row's chunk count is a
-//              multiple of 8 but not 16, so the XOR stays inside the row), which
-//              keeps fragment and transpose reads free of bank conflicts.
-enum Staging { STAGE_REG = 0, STAGE_DMA = 1 };
+// Operand stages of KB k values (32 or 64) in LDS, filled by buffer_load ... lds:
+// lane L of a wave instruction fills bytes [16 L, 16 L + 16) of a 1 KB block, so
+// rows are unpadded and 16-byte chunks are XOR-swizzled instead (k-major: chunk ^
+// ((row / P) mod Q) with P rows per 256 bytes and Q chunks per row; mn-major: chunk
+// ^ s (k mod 4) with s = 4, or 2 when a row's chunk count is a multiple of 8 but
+// not 16, so the XOR stays inside the row), which keeps fragment and transpose
+// reads free of bank conflicts.
 
 // XOR applied to the 16-byte chunk index of k-row k of an mn-major DMA stage.
 template <int ROWS>
@@ -388,17 +383,10 @@ __device__ __forceinline__ int mn_swizzle(int k) {
     return (k & 3) << SHIFT;
 }
 
-template <int ROWS, bool KMAJOR, int KB, int MODE>
-__host__ __device__ constexpr int stage_elems() {
-    return MODE == STAGE_DMA ? ROWS * KB : (KMAJOR ? ROWS * (KB + 8) : KB * (ROWS + 32));
-}
-
 // Element offset (in bf16) of (mn, k) inside one operand stage.
-template <int ROWS, bool KMAJOR, int KB, int MODE>
+template <int ROWS, bool KMAJOR, int KB>
 __device__ __forceinline__ int lds_off(int mn, int k) {
-    if constexpr (MODE == STAGE_REG) {
-        return KMAJOR ? mn * (KB + 8) + k : k * (ROWS + 32) + mn;
-    } else if constexpr (KMAJOR) {
+    if constexpr (KMAJOR) {
         constexpr int Q = KB / 8, P = 16 / Q;  // chunks per row, rows per 256 bytes
         return mn * KB + (((k >> 3) ^ ((mn / P) % Q)) << 3) + (k & 7);
     } else {
@@ -415,47 +403,7 @@ __device__ __forceinline__ uint32_t vec_off(int ld, int mn, int mn_lim, int k, i
     return ok ? static_cast<uint32_t>(e) * 2u : kOutOfRange;
 }
 
-// --- register staging: ROWS * KB / 8 / NT vectors per thread, consecutive
-// lanes read consecutive 16-byte segments of a row (coalesced).
-template <int ROWS, bool KMAJOR, int KB, int NT>
-struct RegStage {
-    static constexpr int V = ROWS * KB / 8 / NT;
-    static_assert(V * NT * 8 == ROWS * KB, "stage must split evenly over threads");
-    static __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, int ld, int mn0,
-                                                int mn_lim, int k0, int k_lim, uint4 (&r)[V]) {
-        const int tid = threadIdx.x;
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-            if (KMAJOR) {
-                constexpr int VPR = KB / 8;  // vectors per mn row
-                const int q = tid + NT * j;
-                r[j] = buf_load16(rs, vec_off<true>(ld, mn0 + q / VPR, mn_lim, k0 + (q % VPR) * 8, k_lim));
-            } else {
-                constexpr int VPR = ROWS / 8;  // vectors per k row
-                const int q = tid + NT * j;
-                r[j] = buf_load16(rs, vec_off<false>(ld, mn0 + (q % VPR) * 8, mn_lim, k0 + q / VPR, k_lim));
-            }
-        }
-    }
-    static __device__ __forceinline__ void store(uint16_t* s, const uint4 (&r)[V]) {
-        const int tid = threadIdx.x;
-#pragma unroll
-        for (int j = 0; j < V; ++j) {
-            const int q = tid + NT * j;
-            int o;
-            if (KMAJOR) {
-                constexpr int VPR = KB / 8;
-                o = lds_off<ROWS, true, KB, STAGE_REG>(q / VPR, (q % VPR) * 8);
-            } else {
-                constexpr int VPR = ROWS / 8;
-                o = lds_off<ROWS, false, KB, STAGE_REG>((q % VPR) * 8, q / VPR);
-            }
-            *reinterpret_cast<uint4*>(s + o) = r[j];
-        }
-    }
-};
-
-// --- LDS DMA: the operand stage is ROWS * KB / 512 blocks of 1 KB; wave w
+// An operand stage is ROWS * KB / 512 blocks of 1 KB; wave w
 // issues blocks [w * PER, (w + 1) * PER). Lane L of a block holds physical
 // bytes [16 L, 16 L + 16), whose logical (swizzled) position decides what it
 // fetches.
@@ -634,18 +582,18 @@ __device__ __forceinline__ s16x4 lds_read_tr(const uint16_t* p) {
 
 // Operand fragment of v_mfma_f32_32x32x16_bf16 for 32 mn values (lane & 31)
 // x 8 k values (k = 16 * kstep + 8 * (lane >> 5) + 0..7).
-template <int ROWS, bool KMAJOR, int KB, int MODE>
+template <int ROWS, bool KMAJOR, int KB>
 __device__ __forceinline__ bf16x8 read_frag(const uint16_t* s, int blk, int kstep, int lane) {
     if (KMAJOR) {
         const int mn = blk * 32 + (lane & 31), k = kstep * 16 + (lane >> 5) * 8;
-        return *reinterpret_cast<const bf16x8*>(s + lds_off<ROWS, true, KB, MODE>(mn, k));
+        return *reinterpret_cast<const bf16x8*>(s + lds_off<ROWS, true, KB>(mn, k));
     } else {
         // 16-lane group g covers mn [16 (g & 1), +16) and k [8 (g >> 1), +8)
         const int g = lane >> 4, j = lane & 15;
         const int k = kstep * 16 + 8 * (g >> 1) + (j >> 2);
         const int mn = blk * 32 + 16 * (g & 1) + 4 * (j & 3);
-        const s16x4 lo = lds_read_tr(s + lds_off<ROWS, false, KB, MODE>(mn, k));
-        const s16x4 hi = lds_read_tr(s + lds_off<ROWS, false, KB, MODE>(mn, k + 4));
+        const s16x4 lo = lds_read_tr(s + lds_off<ROWS, false, KB>(mn, k));
+        const s16x4 hi = lds_read_tr(s + lds_off<ROWS, false, KB>(mn, k + 4));
         const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
         return __builtin_bit_cast(bf16x8, v);
     }
@@ -671,30 +619,15 @@ __device__ __forceinline__ void gelu_pair(float h, float& g, float& dg) {
     dg = __builtin_fmaf(h, phi, phi_cdf);
 }
 
-// Static description of one bf16 GEMM tiling: BM x BN block tile of WGM x WGN
-// waves, KB-deep stages, NS stages in flight, staging mode.
-template <int BM_, int BN_, int WGM_, int WGN_, int KB_, int NS_, int MODE_, bool PAIR_ = false>
-struct Tile {
-    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, KB = KB_, NS = NS_;
-    static constexpr int MODE = MODE_;
+// The 128 x 128 tile of small weight gradients: four waves as 2 x 2, a ring of four
+// 32-deep stages, two blocks per CU.
+struct SmallTile {
+    static constexpr int BM = 128, BN = 128, WGN = 2, KB = 32, NS = 4;
     static constexpr bool PHASED = false;
-    // PAIR: stages are fetched two at a time (kt + 2 and kt + 3 at each even
-    // kt), so the two 64-byte halves of a 128-byte k-major row segment are
-    // requested back to back and share one cache-line fill
-    static constexpr bool PAIR = PAIR_;
-    static constexpr int NW = WGM * WGN, NT = 64 * NW;
-    static constexpr int WM = BM / WGM, WN = BN / WGN;  // wave tile
-    static constexpr int FM = WM / 32, FN = WN / 32;    // 32 x 32 MFMA blocks per wave
+    static constexpr int NW = 4, NT = 256, WAVES_PER_EU = 2;
+    static constexpr int WM = 64, WN = 64, FM = 2, FN = 2;  // wave tile, in 32 x 32 blocks
     static constexpr int KSTEPS = KB / 16;
-    // two waves per SIMD: 8-wave tiles, or two 4-wave blocks per CU when their
-    // stage rings fit half the LDS; one 4-wave block per CU otherwise
     static constexpr int RING_BYTES = NS * (BM + BN) * KB * 2;
-    static constexpr int WAVES_PER_EU = (NW == 8 || RING_BYTES <= 80 * 1024) ? 2 : 1;
-    static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile must be whole 32 x 32 blocks");
-    static_assert(KSTEPS % 2 == 0, "fragment double buffering needs an even step count");
-    static_assert(MODE == STAGE_DMA || NS == 2, "register staging runs two stages");
-    static_assert(NS >= 2 && NS <= 5, "stage ring size");
-    static_assert(!PAIR || (NS == 4 && MODE == STAGE_DMA), "paired fetch runs a ring of four");
 };
 
 // A 256-row tile whose 64-deep stages are worked through in PB phases, one per
@@ -703,8 +636,7 @@ struct Tile {
 template <int PB_>
 struct PhaseTile {
     static constexpr int PB = PB_;
-    static constexpr int BM = 256, BN = 64 * PB, WGM = 4, WGN = 2, KB = 64, NS = 2;
-    static constexpr int MODE = STAGE_DMA;
+    static constexpr int BM = 256, BN = 64 * PB, WGN = 2, KB = 64, NS = 2;
     static constexpr bool PHASED = true;
     static constexpr int NW = 8, NT = 512, WAVES_PER_EU = 2;
     static constexpr int WM = 64, FM = 2;
@@ -719,42 +651,31 @@ struct PhaseTile {
 // columns and one 32-row block, each wave's LDS in a 16 KB buffer of its own.
 template <int COLS>
 struct LightShape {
-    static constexpr int BM = 32, BN = 64 * COLS, WGM = 1, WGN = COLS, NS = 8, NW = 8, NT = 512;
+    static constexpr int BM = 32, BN = 64 * COLS, WGN = COLS, NS = 8, NW = 8, NT = 512;
     static constexpr int WM = 32, WN = 64, FM = 1, FN = 2;
     static constexpr int RING_BYTES = NS * 16384;
     static constexpr bool PHASED = false;
 };
 
-// Per-GEMM static sizes derived from a tiling and the operand layouts.
-template <class T, bool A_KMAJOR, bool B_KMAJOR, int EPI>
+// Static sizes of gemm_epilogue, for small and light tiles: wave w parks one 32-row
+// block of its outputs, all outputs at once, in 16 KB buffer w. Staged rows are
+// padded by 16 bytes: 16-byte aligned for the row reads (a 136-byte bf16 row left
+// every other row's reads misaligned, which the LDS serves with stalls) and off the
+// banks of the row above.
+template <class T, int EPI>
 struct GemmCfg {
     static constexpr int BUF_BYTES = T::RING_BYTES / T::NS;  // one stage buffer
     static constexpr bool F32_OUT = EPI == EPI_F32;
     static constexpr int OUTS = EPI == EPI_FWD1 ? 2 : 1;
-    // Epilogue staging: wave w parks its outputs in stage buffer w mod NS; IPP
-    // of its FM 32-row blocks per pass, all outputs of those rows at once when
-    // they fit (a second output pass would recompute the activation).
-    // staged rows padded by 16 bytes: 16-byte aligned for the row reads (a
-    // 136-byte bf16 row left every other row's reads misaligned, which the
-    // LDS serves with stalls) and off the banks of the row above
     static constexpr int ELEM = F32_OUT ? 4 : 2;
     static constexpr int EP_LD = T::WN + 16 / ELEM;
-    static constexpr int EP_ROWBLK = 32 * EP_LD * ELEM;
-    static constexpr int WAVES_PER_BUF = (T::NW + T::NS - 1) / T::NS;
-    static constexpr bool fits(int outs, int blocks) {
-        return outs * blocks * EP_ROWBLK * WAVES_PER_BUF <= BUF_BYTES;
-    }
-    static constexpr int EP_OUTS_AT_ONCE = fits(OUTS, 1) ? OUTS : 1;
-    static constexpr int IPP = fits(EP_OUTS_AT_ONCE, T::FM) ? T::FM
-                             : (fits(EP_OUTS_AT_ONCE, T::FM / 2) ? T::FM / 2 : 1);
-    static constexpr int EP_TILE = IPP * EP_ROWBLK;
-    static_assert(fits(EP_OUTS_AT_ONCE, IPP), "epilogue staging exceeds LDS");
-    static_assert(!F32_OUT || !A_KMAJOR, "row sums read an mn-major A tile");
+    static constexpr int EP_TILE = 32 * EP_LD * ELEM;
+    static_assert(T::NW <= T::NS && OUTS * EP_TILE <= BUF_BYTES, "epilogue staging exceeds LDS");
     static_assert(!F32_OUT || T::NT % T::BM == 0, "row sums give each A row NT / BM threads");
     static_assert(!F32_OUT || T::NT * 4 <= BUF_BYTES, "row-sum partials fit one stage buffer");
 };
 
-template <class T, bool A_KMAJOR, bool B_KMAJOR, int MODE>
+template <class T>
 struct Frags {
     static constexpr int FM = T::FM, FN = T::FN;
     bf16x8 a[FM], b[FN];
@@ -765,10 +686,10 @@ struct Frags {
         if constexpr (FL > 0) {
 #pragma unroll
             for (int i = 0; i < FL; ++i)
-                a[i] = read_frag<T::BM, A_KMAJOR, T::KB, MODE>(As, wm * FM + i, ks, lane);
+                a[i] = read_frag<T::BM, false, T::KB>(As, wm * FM + i, ks, lane);
 #pragma unroll
             for (int j = 0; j < FN; ++j)
-                b[j] = read_frag<T::BN, B_KMAJOR, T::KB, MODE>(Bs, wn * FN + j, ks, lane);
+                b[j] = read_frag<T::BN, false, T::KB>(Bs, wn * FN + j, ks, lane);
         }
     }
 };
@@ -820,7 +741,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, f32x16 (&acc)[T
                                               int M, int N, int m0, int n0, int fm_live) {
     constexpr int FM = T::FM, FN = T::FN, WM = T::WM, WN = T::WN, BM_ = T::BM;
     constexpr int EP_LD = CFG::EP_LD, ELEM = CFG::ELEM, EP_TILE = CFG::EP_TILE;
-    constexpr int IPP = CFG::IPP, OUTS = CFG::OUTS, EPO = CFG::EP_OUTS_AT_ONCE;
+    constexpr int OUTS = CFG::OUTS;
     constexpr bool F32_OUT = CFG::F32_OUT;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / T::WGN, wn = wave % T::WGN;
@@ -841,107 +762,91 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, f32x16 (&acc)[T
         }
     }
 
-    char* ep = reinterpret_cast<char*>(ep_buf) + (wave / T::NS) * EPO * EP_TILE;
+    char* ep = reinterpret_cast<char*>(ep_buf);
     constexpr int SEG = 16 / ELEM;                 // elements per 16-byte segment
     constexpr int LANES_PER_ROW = WN / SEG;
-    constexpr int ROWS_PER_PASS = 64 / LANES_PER_ROW;  // lanes past ROWS_PER_PASS rows idle
-    constexpr int PASSES = (IPP * 32 + ROWS_PER_PASS - 1) / ROWS_PER_PASS;
-    static_assert(LANES_PER_ROW <= 64 && WN % SEG == 0, "epilogue row split");
+    constexpr int ROWS_PER_PASS = 64 / LANES_PER_ROW;
+    constexpr int PASSES = 32 / ROWS_PER_PASS;
+    static_assert(64 % LANES_PER_ROW == 0 && WN % SEG == 0, "epilogue row split");
 
 #pragma unroll
-    for (int i0 = 0; i0 < FM; i0 += IPP) {
-        if (i0 >= fm_live) break;  // the wave's remaining rows are past M
-        // saved gelu'(H) of this pass's rows, all loads in flight together
-        uint2 aux[EPI == EPI_GELU_GRAD ? IPP * FN * 4 : 1];
+    for (int i = 0; i < FM; ++i) {
+        if (i >= fm_live) break;  // the wave's remaining rows are past M
+        // saved gelu'(H) of the block's rows, all loads in flight together
+        uint2 aux[EPI == EPI_GELU_GRAD ? FN * 4 : 1];
         if constexpr (EPI == EPI_GELU_GRAD) {
 #pragma unroll
-            for (int ii = 0; ii < IPP; ++ii)
+            for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int n = n0 + wn * WN + j * 32 + 8 * q + 4 * (lane >> 5);
-                        const int m = m0 + wm * WM + (i0 + ii) * 32 + (lane & 31);
-                        aux[(ii * FN + j) * 4 + q] =
-                            (n < N && m < M) ? *reinterpret_cast<const uint2*>(
-                                                   static_cast<const uint16_t*>(p.aux) +
-                                                   e * p.out_estride +
-                                                   static_cast<size_t>(m) * p.ldo + n)
-                                             : make_uint2(0u, 0u);
-                    }
+                for (int q = 0; q < 4; ++q) {
+                    const int n = n0 + wn * WN + j * 32 + 8 * q + 4 * (lane >> 5);
+                    const int m = m0 + wm * WM + i * 32 + (lane & 31);
+                    aux[j * 4 + q] = (n < N && m < M)
+                                         ? *reinterpret_cast<const uint2*>(
+                                               static_cast<const uint16_t*>(p.aux) +
+                                               e * p.out_estride + static_cast<size_t>(m) * p.ldo + n)
+                                         : make_uint2(0u, 0u);
+                }
         }
+        // Stage 1: register 4q + r of lane l holds C[m][n + r] with m = 32 i + l % 32,
+        // n = 32 j + 8 q + 4 (l / 32) inside the wave tile.
 #pragma unroll
-        for (int o0 = 0; o0 < OUTS; o0 += EPO) {
-            // Stage 1: register 4q + r of lane l holds C[m][n + r] with
-            // m = 32 i + l % 32, n = 32 j + 8 q + 4 (l / 32) inside the wave tile.
+        for (int j = 0; j < FN; ++j)
 #pragma unroll
-            for (int ii = 0; ii < IPP; ++ii)
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int i = i0 + ii;
-                        const int ml = ii * 32 + (lane & 31);  // row inside the staged rows
-                        const int nl = j * 32 + 8 * q + 4 * (lane >> 5);
-                        const f32x16& v = acc[i][j];
-                        float r[4] = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-                        if constexpr (F32_OUT) {
-                            *reinterpret_cast<float4*>(reinterpret_cast<float*>(ep) + ml * EP_LD +
-                                                       nl) = make_float4(r[0], r[1], r[2], r[3]);
-                        } else {
-                            // (the bias of EPI_FWD1 / EPI_BIAS is already in acc)
-                            if constexpr (EPI == EPI_GELU_GRAD) {
-                                const uint2 gg = aux[(ii * FN + j) * 4 + q];
-                                r[0] *= bf16_to_f32(gg.x & 0xFFFFu);
-                                r[1] *= bf16_to_f32(gg.x >> 16);
-                                r[2] *= bf16_to_f32(gg.y & 0xFFFFu);
-                                r[3] *= bf16_to_f32(gg.y >> 16);
-                            }
-                            uint16_t* t0 = reinterpret_cast<uint16_t*>(ep) + ml * EP_LD + nl;
-                            if constexpr (EPI == EPI_FWD1) {
-                                float g[4], dg[4];
-#pragma unroll
-                                for (int c = 0; c < 4; ++c) gelu_pair(r[c], g[c], dg[c]);
-#pragma unroll
-                                for (int o = 0; o < EPO; ++o) {
-                                    const float* src = (o0 + o == 0) ? g : dg;
-                                    *reinterpret_cast<uint2*>(t0 + o * (EP_TILE / 2)) =
-                                        make_uint2(pack_bf16x2(src[0], src[1]),
-                                                   pack_bf16x2(src[2], src[3]));
-                                }
-                            } else {
-                                *reinterpret_cast<uint2*>(t0) =
-                                    make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
-                            }
-                        }
+            for (int q = 0; q < 4; ++q) {
+                const int ml = lane & 31;  // row inside the staged rows
+                const int nl = j * 32 + 8 * q + 4 * (lane >> 5);
+                const f32x16& v = acc[i][j];
+                float r[4] = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+                if constexpr (F32_OUT) {
+                    *reinterpret_cast<float4*>(reinterpret_cast<float*>(ep) + ml * EP_LD + nl) =
+                        make_float4(r[0], r[1], r[2], r[3]);
+                } else {
+                    // (the bias of EPI_FWD1 / EPI_BIAS is already in acc)
+                    if constexpr (EPI == EPI_GELU_GRAD) {
+                        const uint2 gg = aux[j * 4 + q];
+                        r[0] *= bf16_to_f32(gg.x & 0xFFFFu);
+                        r[1] *= bf16_to_f32(gg.x >> 16);
+                        r[2] *= bf16_to_f32(gg.y & 0xFFFFu);
+                        r[3] *= bf16_to_f32(gg.y >> 16);
                     }
+                    uint16_t* t0 = reinterpret_cast<uint16_t*>(ep) + ml * EP_LD + nl;
+                    if constexpr (EPI == EPI_FWD1) {
+                        float g[4], dg[4];
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) gelu_pair(r[c], g[c], dg[c]);
+                        *reinterpret_cast<uint2*>(t0 + EP_TILE / 2) =
+                            make_uint2(pack_bf16x2(dg[0], dg[1]), pack_bf16x2(dg[2], dg[3]));
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) r[c] = g[c];
+                    }
+                    *reinterpret_cast<uint2*>(t0) =
+                        make_uint2(pack_bf16x2(r[0], r[1]), pack_bf16x2(r[2], r[3]));
+                }
+            }
 
-            // Stage 2: staged rows out in 16-byte segments.
-            const int cl = (lane % LANES_PER_ROW) * SEG;
-            const int n = n0 + wn * WN + cl;
-            const int lrow = lane / LANES_PER_ROW;
+        // Stage 2: staged rows out in 16-byte segments.
+        const int cl = (lane % LANES_PER_ROW) * SEG;
+        const int n = n0 + wn * WN + cl;
 #pragma unroll
-            for (int o = 0; o < EPO; ++o) {
-                char* dst_base = static_cast<char*>(o0 + o == 0 ? p.out : p.out2);
+        for (int o = 0; o < OUTS; ++o) {
+            char* dst_base = static_cast<char*>(o == 0 ? p.out : p.out2);
 #pragma unroll
-                for (int pass = 0; pass < PASSES; ++pass) {
-                    const int ml = pass * ROWS_PER_PASS + lrow;
-                    if (lrow >= ROWS_PER_PASS || ml >= IPP * 32) continue;
-                    const int m = m0 + wm * WM + i0 * 32 + ml;
-                    const uint4 v = *reinterpret_cast<const uint4*>(ep + o * EP_TILE +
-                                                                    (ml * EP_LD + cl) * ELEM);
-                    if (m < M && n < N) {
-                        v4i32* dst = reinterpret_cast<v4i32*>(
-                            dst_base +
-                            (e * p.out_estride + static_cast<size_t>(m) * p.ldo + n) * ELEM);
-                        // weight gradients are not read again by the layer: streaming
-                        // stores keep them from displacing cached activations (the f32
-                        // write-back cost a fifth of the weight-gradient GEMM, measured alone)
-                        if constexpr (F32_OUT)
-                            __builtin_nontemporal_store(__builtin_bit_cast(v4i32, v), dst);
-                        else
-                            *dst = __builtin_bit_cast(v4i32, v);
-                    }
+            for (int pass = 0; pass < PASSES; ++pass) {
+                const int ml = pass * ROWS_PER_PASS + lane / LANES_PER_ROW;
+                const int m = m0 + wm * WM + i * 32 + ml;
+                const uint4 v =
+                    *reinterpret_cast<const uint4*>(ep + o * EP_TILE + (ml * EP_LD + cl) * ELEM);
+                if (m < M && n < N) {
+                    v4i32* dst = reinterpret_cast<v4i32*>(
+                        dst_base + (e * p.out_estride + static_cast<size_t>(m) * p.ldo + n) * ELEM);
+                    // weight gradients are not read again by the layer: streaming
+                    // stores keep them from displacing cached activations (the f32
+                    // write-back cost a fifth of the weight-gradient GEMM, measured alone)
+                    if constexpr (F32_OUT)
+                        __builtin_nontemporal_store(__builtin_bit_cast(v4i32, v), dst);
+                    else
+                        *dst = __builtin_bit_cast(v4i32, v);
                 }
             }
         }
@@ -961,37 +866,28 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, f32x16 (&acc)[T
 // epilogue of their one live row block.
 constexpr int kLightGroups = 2;  // 64-deep k groups in flight per wave
 
-// LDS-typed views of the stage buffers for the light path (a pointer selected
-// among the buffers at run time would otherwise become a flat pointer, whose
+// LDS-typed views of a tile's arrays (a pointer selected
+// among the arrays at run time would otherwise become a flat pointer, whose
 // accesses wait on the vector-memory counter too)
 typedef __attribute__((address_space(3))) uint16_t lds_u16;
 typedef __attribute__((address_space(3))) v4i32 lds_v4;
 typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 typedef __attribute__((address_space(3))) float lds_f32;
 
-// The kernel's LDS arrays as the light path's buffers: the ring's stage
-// buffers, or 16 KB pieces of a phased tile's arrays (a select over values: a
-// closure or array of the buffers' addresses would sit in scratch memory)
+// A phased tile's LDS arrays, and their eight 16 KB pieces (a select over values:
+// a closure or array of the arrays' addresses would sit in scratch memory)
 struct LdsArrays {
     uint16_t *b0, *b1, *b2, *b3, *b4, *b5, *b6;
 };
-template <int NS>
 __device__ __forceinline__ lds_u16* pick_lds(int i, const LdsArrays& a) {
     uint16_t* b = a.b0;
-    if constexpr (NS == 8) {
-        if (i == 1) b = a.b0 + 8192;
-        if (i == 2) b = a.b1;
-        if (i == 3) b = a.b1 + 8192;
-        if (i == 4) b = a.b6;
-        if (i == 5) b = a.b6 + 8192;
-        if (i == 6) b = a.b2;
-        if (i == 7) b = a.b4;
-    } else {
-        if (NS > 1 && i == 1) b = a.b1;
-        if (NS > 2 && i == 2) b = a.b2;
-        if (NS > 3 && i == 3) b = a.b3;
-        if (NS > 4 && i == 4) b = a.b4;
-    }
+    if (i == 1) b = a.b0 + 8192;
+    if (i == 2) b = a.b1;
+    if (i == 3) b = a.b1 + 8192;
+    if (i == 4) b = a.b6;
+    if (i == 5) b = a.b6 + 8192;
+    if (i == 6) b = a.b2;
+    if (i == 7) b = a.b4;
     return (lds_u16*)(b);
 }
 
@@ -1027,18 +923,16 @@ __device__ __forceinline__ void light_tile(const GemmArgs& p, __amdgpu_buffer_rs
                                            __amdgpu_buffer_rsrc_t rb_rs, int e, int M, int N,
                                            int K, int m0, int n0, int part, int nparts,
                                            const LdsArrays& arrays) {
-    constexpr int FM = T::FM, FN = T::FN, WN = T::WN, WGN = T::WGN, NS = T::NS;
+    constexpr int FM = T::FM, FN = T::FN, WN = T::WN, WGN = T::WGN;
     constexpr int U = kLightGroups;
     constexpr int LD = 64 + 8;          // LDS row: 64 elements + 16 bytes (rows on other banks)
     constexpr int A_EL = 32 * LD;       // A block: 32 rows x 64 k
     constexpr int B_EL = 64 * LD;       // B block: 64 n x 64 k (k-major) or 64 k x 64 n
     constexpr int W_EL = A_EL + B_EL;   // one wave's LDS block
-    constexpr int WPB = (T::NW + NS - 1) / NS;  // waves per stage buffer
     constexpr int PB = FN * 16 * 64;    // floats of one wave's partial sums
     static_assert(WN == 64 && FN == 2, "light tiles: 64-column wave tiles");
-    static_assert(WPB * W_EL * 2 <= CFG::BUF_BYTES, "wave LDS blocks fit the stage buffers");
-    static_assert((T::NW - 1 + NS - 1) / NS * PB * 4 <= CFG::BUF_BYTES,
-                  "partial sums fit the stage buffers");
+    static_assert(W_EL * 2 <= CFG::BUF_BYTES && PB * 4 <= CFG::BUF_BYTES,
+                  "a wave's LDS block and its partial sums fit its buffer");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     // the part's columns are `cols` wave columns; wave w takes column c and k
     // slice sl of ks (slice 0 holds the sums)
@@ -1102,9 +996,8 @@ __device__ __forceinline__ void light_tile(const GemmArgs& p, __amdgpu_buffer_rs
             for (int r = 0; r < 4; ++r) lacc[j][4 * q + r] = b4[r];
         }
 
-    auto lds_buf = [=](int i) { return pick_lds<NS>(i, arrays); };
-    // wave w's LDS block: stage buffer w mod NS, slot w / NS
-    lds_u16* const as = lds_buf(wave % NS) + (wave / NS) * W_EL;
+    // wave w's LDS block: buffer w
+    lds_u16* const as = pick_lds(wave, arrays);
     lds_u16* const bs = as + A_EL;
     // (group by group, as the loop refills them: each group then waits for its
     // own loads only, also on the loop's first trip)
@@ -1163,11 +1056,9 @@ __device__ __forceinline__ void light_tile(const GemmArgs& p, __amdgpu_buffer_rs
         }
     }
 
-    // slices 1.. park their sums (slot s = (sl - 1) cols + c: stage buffer s
-    // mod NS); every wave is past its LDS block first
-    auto slot = [&](int s) -> lds_f32* {
-        return reinterpret_cast<lds_f32*>(lds_buf(s % NS)) + (s / NS) * PB;
-    };
+    // slices 1.. park their sums (slice sl, column c: buffer (sl - 1) cols + c);
+    // every wave is past its LDS block first
+    auto slot = [&](int s) { return reinterpret_cast<lds_f32*>(pick_lds(s, arrays)); };
     __syncthreads();
     if (sl > 0) {
         lds_f32* const dst = slot((sl - 1) * cols + c);
@@ -1196,7 +1087,7 @@ __device__ __forceinline__ void light_tile(const GemmArgs& p, __amdgpu_buffer_rs
         for (int j = 0; j < FN; ++j) acc[0][j] = lacc[j];
     }
     __syncthreads();  // the sums are read before the epilogue stages outputs over them
-    uint16_t* const ep = (uint16_t*)(lds_buf(wave % NS));  // (an LDS pointer, seen as such)
+    uint16_t* const ep = (uint16_t*)(pick_lds(wave, arrays));  // (an LDS pointer, seen as such)
     gemm_epilogue<T, CFG, EPI>(p, acc, arrays.b0, ep, 0.0f, false, e, M, N, m0, n0w, sl == 0 ? 1 : 0);
 }
 
@@ -1365,9 +1256,9 @@ __device__ __forceinline__ void phase_epilogue_f32(const GemmArgs& p,
         }
         return;
     }
-    lds_u16* const lo = pick_lds<8>(2 * wm, arrays);
-    lds_u16* const hi = pick_lds<8>(2 * wm + 1, arrays);
-    lds_u16* const mine = pick_lds<8>(wave, arrays);
+    lds_u16* const lo = pick_lds(2 * wm, arrays);
+    lds_u16* const hi = pick_lds(2 * wm + 1, arrays);
+    lds_u16* const mine = pick_lds(wave, arrays);
     const int r = lane & 15, n = n0 + 4 * lane;
     lds_u16* const put = ((lane & 16) ? hi : lo) + r * ROW;
 #pragma unroll
@@ -1591,13 +1482,13 @@ __device__ __forceinline__ void phase_tile(const GemmArgs& p, __amdgpu_buffer_rs
         auto read_a = [&](const uint16_t* as, int ks) {
 #pragma unroll
             for (int i = 0; i < FL; ++i)
-                fa[i][ks] = read_frag<T::BM, A_KMAJOR, KB, STAGE_DMA>(as, wm * FM + i, ks, lane);
+                fa[i][ks] = read_frag<T::BM, A_KMAJOR, KB>(as, wm * FM + i, ks, lane);
         };
         if constexpr (FL > 0) {
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) {
                 read_a(a0, ks);
-                fb[0][ks] = read_frag<64, B_KMAJOR, KB, STAGE_DMA>(bl0, wn, ks, lane);
+                fb[0][ks] = read_frag<64, B_KMAJOR, KB>(bl0, wn, ks, lane);
             }
         }
         // stage kt: A in ac, the next stage's in an; S = kt mod 2
@@ -1619,7 +1510,7 @@ __device__ __forceinline__ void phase_tile(const GemmArgs& p, __amdgpu_buffer_rs
                 auto next_b = [&](int ks) {
                     if constexpr (FL > 0)
                         fb[cur ^ 1][ks] =
-                            read_frag<64, B_KMAJOR, KB, STAGE_DMA>(bs, wn, ks, lane);
+                            read_frag<64, B_KMAJOR, KB>(bs, wn, ks, lane);
                 };
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks) {
@@ -1683,29 +1574,156 @@ __device__ __forceinline__ void phase_tile(const GemmArgs& p, __amdgpu_buffer_rs
         phase_epilogue<T, EPI>(p, acc, stg, e, M, N, m0, n0, fm_live);
 }
 
-// One BM x BN output tile of expert e per block of WGM x WGN waves, each
-// (BM/WGM) x (BN/WGN) as 32 x 32 MFMA blocks; tiles are dealt to the 8 XCDs
-// in chunks of neighbouring tiles (shared operand panels in each XCD's L2).
-//
-// Pipeline over KB-deep k-stages, one barrier per stage, NS stage buffers
+// One SmallTile of a weight gradient: wave w = (wm, wn) accumulates 64 x 64 as 32 x 32
+// blocks. Pipeline over 32-deep k-stages, one barrier per stage, four stage buffers
 // (separate LDS arrays, so every access names its buffer statically):
-//   issue the loads of stage kt + NS - 1 (DMA: straight into the buffer that
-//     stage kt - 1 used; REG: into registers, written to the other buffer
-//     before the barrier)
-//   steps 0 .. KSTEPS-2: read fragments of step s+1   | MFMAs of step s
+//   issue the loads of stage kt + 3 (into the buffer that stage kt - 1 used)
+//   read fragments of step 1                      | MFMAs of step 0
 //   wait until stage kt + 1 has landed; barrier
-//   read step-0 fragments of stage kt+1               | MFMAs of the last step
+//   read step-0 fragments of stage kt + 1         | MFMAs of step 1
 // so LDS latency always hides behind a run of MFMAs on held fragments, and
-// HBM latency behind NS - 1 stages of MFMAs. The stage count is rounded up to
-// a multiple of NS so the ring unrolls with static buffers; the padding
+// HBM latency behind three stages of MFMAs. The stage count is rounded up to
+// a multiple of four so the ring unrolls with static buffers; the padding
 // stages load zeros (out of range) and skip their MFMAs.
-// SCHED = 0: one tile per block, the grid dealt over the (live) tile list;
-// SCHED = 1: persistent blocks, each expert owning the number of blocks the
-// fill-clamp-refill quota gives it, each block taking every units-th tile
-// of its expert.
-// GATHER = 1: operand A's rows are gathered token rows of x (the
-// up-projection fused with the dispatch); GATHER = 2: operand B's k rows are
-// (the input-weight gradient, problems with a token list).
+// GS = 2: operand B's k rows are gathered.
+template <int GS>
+__device__ __forceinline__ void ring_tile(const GemmArgs& p, __amdgpu_buffer_rsrc_t ra_rs,
+                                          __amdgpu_buffer_rsrc_t rb_rs, int e, int M, int N, int K,
+                                          int m0, int n0, int tn, uint16_t* buf0, uint16_t* buf1,
+                                          uint16_t* buf2, uint16_t* buf3, uint32_t* tok_s) {
+    using T = SmallTile;
+    using CFG = GemmCfg<T, EPI_F32>;
+    constexpr int KB = T::KB, NS = T::NS, NT = T::NT, FM = T::FM, FN = T::FN;
+    constexpr int KSTEPS = T::KSTEPS, AE = T::BM * KB;
+    static_assert(NS == 4 && KSTEPS == 2, "the ring below");
+    using DA = DmaStage<T::BM, false, KB, NT>;
+    using DB = DmaStage<T::BN, false, KB, NT>;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = wave_id();
+    const int wm = wave / T::WGN, wn = wave % T::WGN;
+    // 32-row blocks of this wave's rows that lie inside M
+    const int fm_live = __builtin_amdgcn_readfirstlane(
+        min(FM, max(0, (M - m0 - wm * T::WM + 31) / 32)));
+    // Gathered k rows (new ones every stage): the expert's token list in LDS, each
+    // lane's offsets for the next stage read one stage ahead.
+    uint32_t bk[GS == 2 ? DB::PER : 1], bcol[GS == 2 ? DB::PER : 1];
+    if constexpr (GS == 2) {
+        // the expert's k rows as byte offsets of their rows of x, and the
+        // sentinel past K up to the last row the ring prefetches (so the
+        // stage loop tests no bound)
+        const int kfill = ((K + NS * KB - 1) / (NS * KB) + 1) * NS * KB;
+        for (int i = tid; i < kfill; i += NT)
+            tok_s[i] = i < K ? static_cast<uint32_t>(p.tok[e * p.tok_estride + i]) *
+                                   (2u * static_cast<uint32_t>(p.b.ld))
+                             : kGatherSentinel;
+        __syncthreads();
+        DB::krow_cols(n0, N, bcol);
+#pragma unroll
+        for (int q = 0; q < DB::PER; ++q) bk[q] = tok_s[DB::lane_row(q)];
+    }
+    // the first n-tile also sums its A rows (bias gradient): thread t adds row
+    // t % BM over k slice t / BM of each stage
+    const bool row_sum = p.bsum != nullptr && tn == 0;
+    constexpr int RS_K = KB / (NT / T::BM);
+    float rsum = 0.0f;
+
+    // DMA wave instructions per stage; stage kt + 1 has landed once at most
+    // NS - 2 later stages are still in flight
+    constexpr int WAIT_IMM = VmWait<(NS - 2) * (DA::PER + DB::PER)>::imm;
+    const int nk = (K + KB - 1) / KB;
+    const int nk_ring = (nk + NS - 1) / NS * NS;
+    // stages [0, n_inside) lie inside K: their loads differ in a scalar only
+    // (the k-row gather has new rows every stage)
+    const int n_inside = K / KB;
+    uint32_t aoff[DA::PER], boff[DB::PER];
+    DA::lane_offs(p.a.ld, m0, M, aoff);
+    if constexpr (GS != 2) DB::lane_offs(p.b.ld, n0, N, boff);
+    const uint32_t a_step = KB * p.a.ld * 2, b_step = KB * p.b.ld * 2;
+    auto issue = [&](int kt, uint16_t* dst) {
+        const bool inside = kt < n_inside;
+        if (inside) DA::issue_inside(ra_rs, aoff, kt * a_step, dst);
+        else DA::issue(ra_rs, p.a.ld, m0, M, kt * KB, K, dst);
+        if constexpr (GS == 2) {
+            DB::issue_krows(rb_rs, bk, bcol, dst + AE);
+            // stages are issued in order: the next one's k rows
+#pragma unroll
+            for (int q = 0; q < DB::PER; ++q) bk[q] = tok_s[(kt + 1) * KB + DB::lane_row(q)];
+        } else {
+            if (inside) DB::issue_inside(rb_rs, boff, kt * b_step, dst + AE);
+            else DB::issue(rb_rs, p.b.ld, n0, N, kt * KB, K, dst + AE);
+        }
+    };
+    issue(0, buf0);
+    issue(1, buf1);
+    issue(2, buf2);
+    f32x16 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+    __builtin_amdgcn_s_waitcnt(WAIT_IMM);
+    ring_barrier();
+
+    // The stage loop of a wave with FL row blocks to compute: straight-line,
+    // instantiated for both, one and none of the blocks, since a test per row block
+    // inside the loop would make every block a branch, at which the compiler waits
+    // for the fragments in flight; blocks past the rows of the output are computed
+    // on whatever the stage holds and never stored. Every instantiation meets the
+    // same barriers.
+    Frags<T> f0, f1;
+    auto ring = [&](auto live_blocks) {
+        constexpr int FL = decltype(live_blocks)::value;
+        f0.template read<FL>(buf0, buf0 + AE, wm, wn, 0, lane);
+        // stage kt computes from `cur`, refills `tgt` (the buffer of stage kt - 1)
+        // and leaves the step-0 fragments of `nxt` in f0
+        auto stage = [&](const int kt, uint16_t* cur, uint16_t* nxt, uint16_t* tgt) {
+            issue(kt + NS - 1, tgt);
+            const bool live = kt < nk;  // uniform: ring padding stages skip their MFMAs
+            if (live) {
+                if (row_sum) {
+                    const int mn = tid % T::BM, k0 = (tid / T::BM) * RS_K;
+#pragma unroll
+                    for (int kk = 0; kk < RS_K; ++kk)
+                        rsum += bf16_to_f32(cur[lds_off<T::BM, false, KB>(mn, k0 + kk)]);
+                }
+                f1.template read<FL>(cur, cur + AE, wm, wn, 1, lane);
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_block<FL>(acc, f0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            __builtin_amdgcn_s_waitcnt(WAIT_IMM);
+            ring_barrier();
+            if (live) {
+                f0.template read<FL>(nxt, nxt + AE, wm, wn, 0, lane);
+                __builtin_amdgcn_sched_barrier(0);
+                mfma_block<FL>(acc, f1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        // The ring unrolls four stages per trip with no conditional stage: a skipped
+        // stage would merge a path with loads still in flight into the loop head.
+        for (int kt = 0; kt < nk_ring; kt += NS) {
+            stage(kt, buf0, buf1, buf3);
+            stage(kt + 1, buf1, buf2, buf0);
+            stage(kt + 2, buf2, buf3, buf1);
+            stage(kt + 3, buf3, buf0, buf2);
+        }
+    };
+    if (fm_live > 1) ring(std::integral_constant<int, 2>{});
+    else if (fm_live > 0) ring(std::integral_constant<int, 1>{});
+    else ring(std::integral_constant<int, 0>{});
+    // every wave is done with the operand stages (LDS reads retired, DMA landed)
+    __builtin_amdgcn_s_waitcnt(VmWait<0>::imm);
+    ring_barrier();
+
+    // wave w parks its outputs in stage buffer w (a select over the arrays
+    // themselves keeps the accesses in the LDS address space)
+    uint16_t* const ep = wave == 0 ? buf0 : wave == 1 ? buf1 : wave == 2 ? buf2 : buf3;
+    gemm_epilogue<T, CFG, EPI_F32>(p, acc, buf0, ep, rsum, row_sum, e, M, N, m0, n0, fm_live);
+}
+
 // Elements of the kernel's LDS arrays.
 template <class T, bool A_KMAJOR, bool B_KMAJOR, int EPI, int GATHER>
 constexpr int gemm_lds(int i) {
@@ -1733,6 +1751,16 @@ constexpr int gemm_waves_per_eu() {
     return GATHER == 2 && T::NW == 4 ? 1 : T::WAVES_PER_EU;
 }
 
+// The bf16 GEMM kernel: one output tile of expert e per block; tiles are dealt to
+// the 8 XCDs in chunks of neighbouring tiles (shared operand panels in each XCD's
+// L2).
+// SCHED = 0: one tile per block, the grid dealt over the (live) tile list;
+// SCHED = 1: persistent blocks, each expert owning the number of blocks the
+// fill-clamp-refill quota gives it, each block taking every units-th tile
+// of its expert.
+// GATHER = 1: operand A's rows are gathered token rows of x (the
+// up-projection fused with the dispatch); GATHER = 2: operand B's k rows are
+// (the input-weight gradient, problems with a token list).
 template <class T, bool A_KMAJOR, bool B_KMAJOR, int EPI, int SCHED = 0, int GATHER = 0>
 __global__ __launch_bounds__(T::NT)
 __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu<T, GATHER>(),
@@ -1880,7 +1908,7 @@ void gemm_bf16_kernel(GemmBatch batch) {
                        p.b.estride * 2);
     if constexpr (LIGHT) {
         if (!p.var_k && M - m0 <= 32) {
-            light_tile<LT, GemmCfg<LT, A_KMAJOR, B_KMAJOR, EPI>, B_KMAJOR, EPI, GS>(
+            light_tile<LT, GemmCfg<LT, EPI>, B_KMAJOR, EPI, GS>(
                 p, ra_rs, rb_rs, e, M, N, K, m0, n0, parts ? tm : 0, parts ? lsplit : 1,
                 LdsArrays{buf0, buf1, buf2, buf3, buf4, buf5, buf6});
             return true;
@@ -1889,280 +1917,11 @@ void gemm_bf16_kernel(GemmBatch batch) {
     if constexpr (T::PHASED) {
         phase_tile<T, A_KMAJOR, B_KMAJOR, EPI, GS>(p, ra_rs, rb_rs, e, M, N, K, m0, n0, tn, buf0,
                                                    buf1, buf2, buf3, buf4, buf5, buf6);
-        return true;
     } else {
-    using CFG = GemmCfg<T, A_KMAJOR, B_KMAJOR, EPI>;
-    constexpr int KB = T::KB, NS = T::NS, MODE = T::MODE;
-    constexpr int NT = T::NT, AE = stage_elems<BM_, A_KMAJOR, KB, MODE>(), FM = T::FM, FN = T::FN;
-    constexpr int KSTEPS = T::KSTEPS;
-    // Gathered A rows (the tile's rows, fixed over the k loop): each lane's
-    // row offsets in x, read once. Gathered B k rows (new ones every stage):
-    // the expert's token list in LDS, each lane's offsets for the next
-    // stage read one stage ahead.
-    using DA_ = DmaStage<BM_, A_KMAJOR, KB, T::NT>;
-    using DB_ = DmaStage<BN_, B_KMAJOR, KB, T::NT>;
-    int arow[GS == 1 ? DA_::PER : 1];
-    uint32_t bk[GS == 2 ? DB_::PER : 1], bcol[GS == 2 ? DB_::PER : 1];
-    if constexpr (GS == 1) {
-#pragma unroll
-        for (int q = 0; q < DA_::PER; ++q) {
-            const int r = DA_::lane_row(q);
-            arow[q] = m0 + r < M ? p.tok[e * p.tok_estride + m0 + r] * p.a.ld : -1;
-        }
-    } else if constexpr (GS == 2) {
-        // the expert's k rows as byte offsets of their rows of x, and the
-        // sentinel past K up to the last row the ring prefetches (so the
-        // stage loop tests no bound)
-        const int kfill = ((K + NS * KB - 1) / (NS * KB) + 1) * NS * KB;
-        for (int i = threadIdx.x; i < kfill; i += T::NT)
-            tok_s[i] = i < K ? static_cast<uint32_t>(p.tok[e * p.tok_estride + i]) *
-                                   (2u * static_cast<uint32_t>(p.b.ld))
-                             : kGatherSentinel;
-        __syncthreads();
-        DB_::krow_cols(n0, N, bcol);
-#pragma unroll
-        for (int q = 0; q < DB_::PER; ++q) bk[q] = tok_s[DB_::lane_row(q)];
+        static_assert(!A_KMAJOR && !B_KMAJOR && EPI == EPI_F32, "small tiles: weight gradients");
+        ring_tile<GS>(p, ra_rs, rb_rs, e, M, N, K, m0, n0, tn, buf0, buf1, buf2, buf3, tok_s);
     }
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = wave_id();
-    const int wm = wave / T::WGN, wn = wave % T::WGN;
-    // 32-row blocks of this wave's rows that lie inside M: an expert with a
-    // few rows (a light expert under a skewed load) runs the matrix-core
-    // products, fragment reads and epilogue of those blocks only
-    const int fm_live = __builtin_amdgcn_readfirstlane(
-        min(FM, max(0, (M - m0 - wm * T::WM + 31) / 32)));
-    // weight-gradient GEMMs: the first n-tile also sums its A rows (bias grad);
-    // thread t adds row t % BM over k slice t / BM of each stage
-    const bool row_sum = CFG::F32_OUT && p.bsum != nullptr && tn == 0;
-    constexpr int RS_SPLIT = CFG::F32_OUT ? NT / BM_ : 1;
-    constexpr int RS_K = KB / RS_SPLIT;
-    float rsum = 0.0f;
-
-    f32x16 acc[FM][FN];
-
-    using DA = DmaStage<BM_, A_KMAJOR, KB, NT>;
-    using DB = DmaStage<BN_, B_KMAJOR, KB, NT>;
-    using RA = RegStage<BM_, A_KMAJOR, KB, NT>;
-    using RB = RegStage<BN_, B_KMAJOR, KB, NT>;
-    // DMA wave instructions per stage; stage kt + 1 has landed once at most
-    // NS - 2 later stages are still in flight
-    constexpr int L = DA::PER + DB::PER;
-    constexpr int WAIT_IMM = VmWait<MODE == STAGE_DMA && !T::PAIR ? (NS - 2) * L : 0>::imm;
-    // A k-major A operand's DMA blocks of wave w hold rows [w BM / NW, (w + 1)
-    // BM / NW) of the tile: a wave whose rows all lie past M (an expert with
-    // few rows) issues none of its A loads (those rows are never read: their
-    // products are skipped) and counts only its B loads in its waits
-    constexpr bool SKIP_A = A_KMAJOR && MODE == STAGE_DMA && !T::PAIR;
-    constexpr int WAIT_IMM_B = VmWait<SKIP_A ? (NS - 2) * DB::PER : 0>::imm;
-    const bool skip_a =
-        SKIP_A && __builtin_amdgcn_readfirstlane(m0 + wave * (BM_ / T::NW)) >= M;
-    // paired fetch: after an even stage the pair issued in it is in flight,
-    // after an odd stage the second half of the previous pair
-    constexpr int WAIT_EVEN = VmWait<T::PAIR ? 2 * L : 0>::imm;
-    constexpr int WAIT_ODD = VmWait<T::PAIR ? L : 0>::imm;
-    BiasRegs<T, EPI> bias;
-    bias.load(p, e, N, n0, wn, lane);
-    const int nk = (K + KB - 1) / KB;
-    const int nk_ring = (nk + NS - 1) / NS * NS;
-    Frags<T, A_KMAJOR, B_KMAJOR, MODE> f0, f1;
-    uint4 ra[MODE == STAGE_REG ? RA::V : 1], rb[MODE == STAGE_REG ? RB::V : 1];
-
-    // stages [0, n_inside) lie inside K: their loads differ in a scalar only
-    // (the k-row gather has new rows every stage)
-    const int n_inside = K / KB;
-    uint32_t aoff[MODE == STAGE_DMA ? DA::PER : 1], boff[MODE == STAGE_DMA ? DB::PER : 1];
-    if constexpr (MODE == STAGE_DMA) {
-        if constexpr (GS == 1) DA::lane_offs_rows(arow, aoff);
-        else DA::lane_offs(p.a.ld, m0, M, aoff);
-        if constexpr (GS != 2) DB::lane_offs(p.b.ld, n0, N, boff);
-    }
-    const uint32_t a_step = (A_KMAJOR ? KB : KB * p.a.ld) * 2;
-    const uint32_t b_step = (B_KMAJOR ? KB : KB * p.b.ld) * 2;
-    auto issue = [&](int kt, uint16_t* dst) {
-        const bool inside = kt < n_inside;
-        if (!skip_a) {
-            if (inside) DA::issue_inside(ra_rs, aoff, kt * a_step, dst);
-            else if constexpr (GS == 1) DA::issue_rows(ra_rs, arow, kt * KB, K, dst);
-            else DA::issue(ra_rs, p.a.ld, m0, M, kt * KB, K, dst);
-        }
-        if constexpr (GS == 2) {
-            DB::issue_krows(rb_rs, bk, bcol, dst + AE);
-            // stages are issued in order: the next one's k rows
-#pragma unroll
-            for (int q = 0; q < DB::PER; ++q) bk[q] = tok_s[(kt + 1) * KB + DB::lane_row(q)];
-        } else {
-            if (inside) DB::issue_inside(rb_rs, boff, kt * b_step, dst + AE);
-            else DB::issue(rb_rs, p.b.ld, n0, N, kt * KB, K, dst + AE);
-        }
-    };
-    // wait until stage kt + 1 has landed (this wave's share of it)
-    auto wait_ring = [&]() {
-        if (skip_a) __builtin_amdgcn_s_waitcnt(WAIT_IMM_B);
-        else __builtin_amdgcn_s_waitcnt(WAIT_IMM);
-    };
-    // the accumulators start from the bias where there is one (added once per
-    // output instead of in the epilogue); its loads were issued first, so
-    // waiting for them leaves the first stages in flight
-    auto init_acc = [&]() {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float b4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-                    if constexpr (BiasRegs<T, EPI>::USED) {
-                        const uint2 bb = bias.v[j * 4 + q];
-                        b4[0] = bf16_to_f32(bb.x & 0xFFFFu);
-                        b4[1] = bf16_to_f32(bb.x >> 16);
-                        b4[2] = bf16_to_f32(bb.y & 0xFFFFu);
-                        b4[3] = bf16_to_f32(bb.y >> 16);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) acc[i][j][4 * q + r] = b4[r];
-                }
-    };
-    if constexpr (MODE == STAGE_DMA) {
-        issue(0, buf0);
-        if constexpr (T::PAIR) {
-            issue(1, buf1);
-            init_acc();
-            __builtin_amdgcn_s_waitcnt(WAIT_ODD);
-        } else {
-            if constexpr (NS > 2) issue(1, buf1);
-            if constexpr (NS > 3) issue(2, buf2);
-            if constexpr (NS > 4) issue(3, buf3);
-            init_acc();
-            wait_ring();
-        }
-        ring_barrier();
-    } else {
-        RA::load(ra_rs, p.a.ld, m0, M, 0, K, ra);
-        RB::load(rb_rs, p.b.ld, n0, N, 0, K, rb);
-        init_acc();
-        RA::store(buf0, ra);
-        RB::store(buf0 + AE, rb);
-        __syncthreads();
-    }
-    // The stage loop of a wave with FL row blocks to compute: straight-line,
-    // instantiated for all, half and none of the blocks; blocks past the rows
-    // of the output are computed on whatever the stage holds and never
-    // stored. Every instantiation meets the same barriers. (A test per row
-    // block inside the loop made every block a branch, at which the compiler
-    // waits for the fragments in flight: 115 -> 101 us for the up-projection
-    // and 73 -> 66 us for the down-projection at 12 608 rows over 8 experts,
-    // d = 768, f = 3072; 480 -> 442 and 338 -> 306 us at 49 000 rows over 32.
-    // These figures include the loads' scalar k offsets, issue_inside.)
-    auto ring = [&](auto live_blocks) {
-    constexpr int FL = decltype(live_blocks)::value;
-    f0.template read<FL>(buf0, buf0 + AE, wm, wn, 0, lane);
-
-    // stage kt computes from `cur`, refills `tgt` (the buffer of stage kt - 1;
-    // paired fetch: at even kt, `tgt` and `tgt2` with stages kt + 2 and kt + 3)
-    // and leaves the step-0 fragments of `nxt` in f0
-    auto stage = [&](const int kt, uint16_t* cur, uint16_t* nxt, uint16_t* tgt, uint16_t* tgt2,
-                     auto parity) {
-        constexpr bool EVEN = decltype(parity)::value == 0;
-        if constexpr (T::PAIR) {
-            if constexpr (EVEN) {
-                issue(kt + 2, tgt);
-                issue(kt + 3, tgt2);
-            }
-        } else if constexpr (MODE == STAGE_DMA) {
-            issue(kt + NS - 1, tgt);
-        } else {
-            RA::load(ra_rs, p.a.ld, m0, M, (kt + 1) * KB, K, ra);
-            RB::load(rb_rs, p.b.ld, n0, N, (kt + 1) * KB, K, rb);
-        }
-        const bool live = kt < nk;  // uniform: ring padding stages skip their MFMAs
-        if (live) {
-            if constexpr (CFG::F32_OUT) {
-                if (row_sum) {
-                    const int mn = tid % BM_, k0 = (tid / BM_) * RS_K;
-#pragma unroll
-                    for (int kk = 0; kk < RS_K; ++kk)
-                        rsum += bf16_to_f32(cur[lds_off<BM_, false, KB, MODE>(mn, k0 + kk)]);
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < KSTEPS - 1; ++s) {
-                if (s % 2 == 0) {
-                    f1.template read<FL>(cur, cur + AE, wm, wn, s + 1, lane);
-                    __builtin_amdgcn_sched_barrier(0);
-                    mfma_block<FL>(acc, f0);
-                } else {
-                    f0.template read<FL>(cur, cur + AE, wm, wn, s + 1, lane);
-                    __builtin_amdgcn_sched_barrier(0);
-                    mfma_block<FL>(acc, f1);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        if constexpr (T::PAIR) {
-            __builtin_amdgcn_s_waitcnt(EVEN ? WAIT_EVEN : WAIT_ODD);
-            ring_barrier();
-        } else if constexpr (MODE == STAGE_DMA) {
-            wait_ring();
-            ring_barrier();
-        } else {
-            RA::store(nxt, ra);
-            RB::store(nxt + AE, rb);
-            __syncthreads();
-        }
-        if (live) {
-            // KSTEPS is even: the last step's fragments are in f1
-            f0.template read<FL>(nxt, nxt + AE, wm, wn, 0, lane);
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_block<FL>(acc, f1);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    // The ring unrolls NS stages per trip with no conditional stage: a skipped
-    // stage would merge a path with loads still in flight into the loop head.
-    using P0 = std::integral_constant<int, 0>;
-    using P1 = std::integral_constant<int, 1>;
-    for (int kt = 0; kt < nk_ring; kt += NS) {
-        if constexpr (NS == 2) {
-            stage(kt, buf0, buf1, buf1, buf1, P0{});
-            stage(kt + 1, buf1, buf0, buf0, buf0, P1{});
-        } else if constexpr (NS == 3) {
-            stage(kt, buf0, buf1, buf2, buf2, P0{});
-            stage(kt + 1, buf1, buf2, buf0, buf0, P1{});
-            stage(kt + 2, buf2, buf0, buf1, buf1, P0{});
-        } else if constexpr (NS == 4 && T::PAIR) {
-            stage(kt, buf0, buf1, buf2, buf3, P0{});
-            stage(kt + 1, buf1, buf2, buf0, buf0, P1{});
-            stage(kt + 2, buf2, buf3, buf0, buf1, P0{});
-            stage(kt + 3, buf3, buf0, buf0, buf0, P1{});
-        } else if constexpr (NS == 4) {
-            stage(kt, buf0, buf1, buf3, buf3, P0{});
-            stage(kt + 1, buf1, buf2, buf0, buf0, P1{});
-            stage(kt + 2, buf2, buf3, buf1, buf1, P0{});
-            stage(kt + 3, buf3, buf0, buf2, buf2, P1{});
-        } else {
-            stage(kt, buf0, buf1, buf4, buf4, P0{});
-            stage(kt + 1, buf1, buf2, buf0, buf0, P1{});
-            stage(kt + 2, buf2, buf3, buf1, buf1, P0{});
-            stage(kt + 3, buf3, buf4, buf2, buf2, P1{});
-            stage(kt + 4, buf4, buf0, buf3, buf3, P0{});
-        }
-    }
-    };
-    if (fm_live > FM / 2) ring(std::integral_constant<int, FM>{});
-    else if (FM > 1 && fm_live > 0) ring(std::integral_constant<int, FM / 2>{});
-    else ring(std::integral_constant<int, 0>{});
-    // every wave is done with the operand stages (LDS reads retired, DMA landed)
-    if constexpr (MODE == STAGE_DMA) __builtin_amdgcn_s_waitcnt(VmWait<0>::imm);
-    else __builtin_amdgcn_s_waitcnt(VmWait<63>::imm);
-    ring_barrier();
-
-    // wave w parks its outputs in stage buffer w mod NS (a select over the
-    // arrays themselves keeps the accesses in the LDS address space)
-    const int eb = wave % NS;
-    uint16_t* const ep = eb == 0 ? buf0 : eb == 1 ? buf1 : eb == 2 ? buf2 : eb == 3 ? buf3 : buf4;
-    gemm_epilogue<T, CFG, EPI>(p, acc, buf0, ep, rsum, row_sum, e, M, N, m0, n0, fm_live);
     return true;
-    }
     };
     bool ran;
     if constexpr (GATHER == 0) ran = tile(std::integral_constant<int, 0>{});
@@ -2670,11 +2429,10 @@ void launch_bf16(const Dims& D, const GemmArgs& a, int grid_m_rows, int sched, h
     launch_bf16<T, AK, BK_, EPI, GATHER>(D, &a, &grid_m_rows, 1, sched, st);
 }
 
-// Tilings: 256 x 256, 256 x 192 (fewer idle CUs where an output is d wide),
-// and 128 x 128 on a ring of four 32-deep stages, two blocks per CU.
+// Tilings: 256 x 256 and 256 x 192 (fewer idle CUs where an output is d wide),
+// beside SmallTile.
 using TileBig = PhaseTile<4>;
 using TileNarrow = PhaseTile<3>;
-using TileSmall = Tile<128, 128, 2, 2, 32, 4, STAGE_DMA>;
 
 // Relative cost per tile area of the other tilings (256 x 256 is 1): of the
 // factors 1.0 to 1.6 for 128 x 128 and 1.0 to 1.15 for 256 x 192, those whose choice
@@ -2713,57 +2471,53 @@ void launch_gemm(const Dims& D, const GemmArgs& a, int grid_m_rows, int sched, h
             return;
         }
     }
-    if (D.dtype == VMOE_BF16) {
-        // 256 x 256 tiles (half the operand bytes per flop of 128 x 128) for
-        // the GEMMs whose m is the expert's rows.
-        // (bf16 weight gradients run batched in ffn_bwd_launch; this EPI_F32
-        // case only serves other callers.)
-        if constexpr (EPI == EPI_F32) {
-            launch_bf16<TileSmall, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
-        } else if constexpr (EPI == EPI_BIAS || EPI == EPI_STORE) {
-            // Narrow outputs (N = d_model) give few tiles: 192-column tiles fill
-            // more CUs when that saves a round. (The f-wide outputs have tiles
-            // enough; with 256 x 192 there too the ViT-B/16 expert MLP forward
-            // took 162 -> 168 us, the 17-task step 1211 -> 1231, eight ViT-L/16
-            // images 294 -> 311.)
-            const long long tm = cdiv(grid_m_rows, 256);
-            const double big = tile_cost(D.E * tm * cdiv(a.N, 256), 256, 256, 1.0);
-            const double narrow = tile_cost(D.E * tm * cdiv(a.N, 192), 256, 192, kNarrowCost);
-            if (narrow < big)
-                launch_bf16<TileNarrow, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
-            else
-                launch_bf16<TileBig, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
-        } else {
-            launch_bf16<TileBig, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
-        }
-    } else {
-        // 64 x 64 tiles halve the operand loads a product, 32 x 32 ones give a
-        // launch four times the blocks and the waves more registers: with 64
-        // from three blocks a CU on for the weight gradients (two mn-major
-        // operands; backward at 400 tokens, d = 256, f = 1024, E = 16: 55 us
-        // against 61 with 32) and from twelve on for the others (from three on:
-        // forward 101 -> 111, backward 227 -> 236 at 1576 tokens, d = 384,
-        // f = 1536, E = 8)
-        const long long big = static_cast<long long>(D.E) * cdiv(grid_m_rows, 64) * cdiv(a.N, 64);
-        // With twelve blocks a CU and k up to 224 the waves of the up-projection stand
-        // side by side instead. Forward, split k / side by side: 1000 rows, E = 64,
-        // d = 64, f = 256 110 / 91 us; 4000 rows, E = 16, d = 192, f = 768 558 / 531;
-        // 4000 rows, E = 16, d = 200, f = 800 667 / 639; below: 6 blocks a CU at
-        // d = 192 even, 1000 rows, E = 16, d = 256, f = 1024 239 / 246, d >= 384 slower.
-        if constexpr (EPI == EPI_FWD1) {
-            if (big >= kNumCUs * 12 && a.K <= 224) {
-                const dim3 grid(cdiv(a.N, 64), cdiv(grid_m_rows, 64), D.E);
-                gemm_f32_short_k_kernel<<<grid, 256, 0, st>>>(a);
-                return;
+    // (bf16 weight gradients run batched in ffn_bwd_launch)
+    if constexpr (EPI != EPI_F32) {
+        if (D.dtype == VMOE_BF16) {
+            // 256 x 256 tiles (half the operand bytes per flop of 128 x 128). Outputs
+            // N = d_model wide give few tiles: 192-column tiles fill more CUs when
+            // that saves a round. (The f-wide outputs have tiles enough; with
+            // 256 x 192 there too the ViT-B/16 expert MLP forward took 162 -> 168 us,
+            // the 17-task step 1211 -> 1231, eight ViT-L/16 images 294 -> 311.)
+            if constexpr (EPI == EPI_BIAS || EPI == EPI_STORE) {
+                const long long tm = cdiv(grid_m_rows, 256);
+                const double big = tile_cost(D.E * tm * cdiv(a.N, 256), 256, 256, 1.0);
+                const double narrow = tile_cost(D.E * tm * cdiv(a.N, 192), 256, 192, kNarrowCost);
+                if (narrow < big) {
+                    launch_bf16<TileNarrow, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
+                    return;
+                }
             }
+            launch_bf16<TileBig, AK, BK_, EPI, GATHER>(D, a, grid_m_rows, sched, st);
+            return;
         }
-        if (big >= kNumCUs * (EPI == EPI_F32 ? 3 : 12)) {
+    }
+    // 64 x 64 tiles halve the operand loads a product, 32 x 32 ones give a
+    // launch four times the blocks and the waves more registers: with 64
+    // from three blocks a CU on for the weight gradients (two mn-major
+    // operands; backward at 400 tokens, d = 256, f = 1024, E = 16: 55 us
+    // against 61 with 32) and from twelve on for the others (from three on:
+    // forward 101 -> 111, backward 227 -> 236 at 1576 tokens, d = 384,
+    // f = 1536, E = 8)
+    const long long big = static_cast<long long>(D.E) * cdiv(grid_m_rows, 64) * cdiv(a.N, 64);
+    // With twelve blocks a CU and k up to 224 the waves of the up-projection stand
+    // side by side instead. Forward, split k / side by side: 1000 rows, E = 64,
+    // d = 64, f = 256 110 / 91 us; 4000 rows, E = 16, d = 192, f = 768 558 / 531;
+    // 4000 rows, E = 16, d = 200, f = 800 667 / 639; below: 6 blocks a CU at
+    // d = 192 even, 1000 rows, E = 16, d = 256, f = 1024 239 / 246, d >= 384 slower.
+    if constexpr (EPI == EPI_FWD1) {
+        if (big >= kNumCUs * 12 && a.K <= 224) {
             const dim3 grid(cdiv(a.N, 64), cdiv(grid_m_rows, 64), D.E);
-            gemm_f32_kernel<AK, BK_, EPI, 2><<<grid, 256, 0, st>>>(a);
-        } else {
-            const dim3 grid(cdiv(a.N, 32), cdiv(grid_m_rows, 32), D.E);
-            gemm_f32_kernel<AK, BK_, EPI, 1><<<grid, 256, 0, st>>>(a);
+            gemm_f32_short_k_kernel<<<grid, 256, 0, st>>>(a);
+            return;
         }
+    }
+    if (big >= kNumCUs * (EPI == EPI_F32 ? 3 : 12)) {
+        const dim3 grid(cdiv(a.N, 64), cdiv(grid_m_rows, 64), D.E);
+        gemm_f32_kernel<AK, BK_, EPI, 2><<<grid, 256, 0, st>>>(a);
+    } else {
+        const dim3 grid(cdiv(a.N, 32), cdiv(grid_m_rows, 32), D.E);
+        gemm_f32_kernel<AK, BK_, EPI, 1><<<grid, 256, 0, st>>>(a);
     }
 }
 
@@ -2979,7 +2733,7 @@ vmoe_status ffn_bwd_launch(const Dims& D, const void* xe, const int32_t* counts,
             else if (big <= small)
                 launch_bf16<TileBig, false, false, EPI_F32, GA>(D, both, rows_m, 2, sched, st);
             else
-                launch_bf16<TileSmall, false, false, EPI_F32, GA>(D, both, rows_m, 2, sched, st);
+                launch_bf16<SmallTile, false, false, EPI_F32, GA>(D, both, rows_m, 2, sched, st);
         };
         if (row_token != nullptr) go(std::integral_constant<int, 2>{});
         else go(std::integral_constant<int, 0>{});
