@@ -1205,7 +1205,12 @@ __device__ __forceinline__ void phase_epilogue_f32(const GemmArgs& p,
                                                    const LdsArrays& arrays, int e, int M, int N,
                                                    int m0, int n0, int fm_live) {
     constexpr int PB = T::PB, FM = T::FM, ROW = 128 * PB;  // a staged row, in 16-bit words
-    const int lane = threadIdx.x & 63, wave = wave_id();
+    // (opaque, so that the quota schedule's loop over tiles does not carry the
+    // addresses below through its products: 30 spilled registers, ViT-L/16 step
+    // under quotas 1352 us against 1325)
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    const int wave = wave_id();
     const int wm = wave / T::WGN, wn = wave % T::WGN;
     const int mr = m0 + 64 * wm;
     if (row_sum) {
