@@ -2098,8 +2098,8 @@ __global__ __launch_bounds__(256) void small_rows_kernel(GemmArgs p) {
 // of 14 us, which the weight gradients' first n-tile now sums from its
 // fragments. (k-major fragments straight from memory, 32 rows an instruction:
 // forward 47 us against 50 before, 67 against 53 at d = 200, f = 800.) Layer step
-// of the 788 tokens 219 -> 133 us, expert MLP forward 50 -> 29, backward
-// 121 -> 57; 1576 tokens, k = 3, d = 384, f = 1536, E = 16: 201 -> 153, 441 -> 340.
+// of the 788 tokens 216 -> 126 us, expert MLP forward 49 -> 28, backward
+// 117 -> 54; 1576 tokens, k = 3, d = 384, f = 1536, E = 16: 199 -> 152, 437 -> 297.
 constexpr int kF32Waves = 4;
 constexpr int kF32Ld = 32 + 4;  // LDS row: 32 k and 16 bytes (rows on other banks)
 
@@ -2672,9 +2672,9 @@ vmoe_status ffn_bwd_launch(const Dims& D, const void* xe, const int32_t* counts,
         // tensors: dxe runs on the side stream beside them, so the weight-
         // gradient blocks take the CUs that its partly filled tiles and last
         // round leave idle (bf16, one-tile-per-block schedule, 16 or more
-        // experts: measured 0.90 -> 0.81 ms on the 17-task pool, 1.18 -> 1.14
-        // at E = 32; with 8 evenly loaded experts every tile is full and the
-        // two launches only contend, 0.33 -> 0.34 ms at ViT-B/16)
+        // experts: 17-task step 1254 -> 1213 us, expert-MLP backward of the wide
+        // E = 32 pool 1041 -> 1019; with 8 evenly loaded experts every tile is
+        // full and the two launches only contend, ViT-B/16 step 523 -> 532)
         if (D.dtype == VMOE_BF16 && sched == 0 && D.E >= 16) {
             seq = std::unique_lock<std::mutex>(side_seq_mu);
             side = side_stream();
