@@ -5,8 +5,8 @@
 // are 256 x 256 or 256 x 192 (PhaseTile<>, phase_tile: eight waves, one block
 // per CU, 64-deep stages taken in 64-column phases); small weight gradients
 // take 128 x 128 with four waves on a plain ring of stages (SmallTile, ring_tile,
-// two blocks per CU). A wave accumulates its sub-tile with v_mfma_f32_32x32x16_bf16 in
-// f32. Operands reach LDS through buffer loads that write LDS directly (16
+// two blocks per CU); a few rows an expert take small_rows_kernel forward. A wave
+// accumulates its sub-tile with v_mfma_f32_32x32x16_bf16 in f32. Operands reach LDS through buffer loads that write LDS directly (16
 // bytes per lane, out-of-range offsets read as zero, so ragged tails need no
 // branch); later stages' loads stay in flight across the barriers (partial
 // vmcnt waits).
@@ -29,8 +29,9 @@
 // 256 CUs times the tile area, scaled by a per-shape efficiency.
 //
 // f32 path: 32 x 32 or 64 x 64 tiles on the f32 matrix cores
-// (v_mfma_f32_32x32x2f32), four waves splitting k, operands straight from
-// memory, with the same operand and epilogue description (the accuracy path).
+// (v_mfma_f32_32x32x2f32), four waves splitting k (side by side where k is short
+// and tiles are many), with the same operand and epilogue description (the
+// accuracy path).
 #include <mutex>
 #include <type_traits>
 
