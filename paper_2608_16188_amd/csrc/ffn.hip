@@ -29,9 +29,8 @@
 // 256 CUs times the tile area, scaled by a per-shape efficiency.
 //
 // f32 path: 32 x 32 or 64 x 64 tiles on the f32 matrix cores
-// (v_mfma_f32_32x32x2f32), four waves splitting k (side by side where k is short
-// and tiles are many), with the same operand and epilogue description (the
-// accuracy path).
+// (v_mfma_f32_32x32x2f32), four waves splitting k, with the same operand and
+// epilogue description (the accuracy path).
 #include <mutex>
 #include <type_traits>
 
@@ -2101,6 +2100,10 @@ __global__ __launch_bounds__(256) void small_rows_kernel(GemmArgs p) {
 // forward 47 us against 50 before, 67 against 53 at d = 200, f = 800.) Layer step
 // of the 788 tokens 216 -> 126 us, expert MLP forward 49 -> 28, backward
 // 117 -> 54; 1576 tokens, k = 3, d = 384, f = 1536, E = 16: 199 -> 152, 437 -> 297.
+// (Up-projections of a short k and very many tiles take 3 to 10 % longer than with
+// the waves side by side, 4000 rows, E = 64, d = 64, f = 256 355 -> 399 us, and err
+// two thirds to half as much: 9.7e-8 against 1.6e-7; with four sums a wave, to err
+// the same, side by side takes 0.93 to 1.04 times the split's time.)
 constexpr int kF32Waves = 4;
 constexpr int kF32Ld = 32 + 4;  // LDS row: 32 k and 16 bytes (rows on other banks)
 
@@ -2326,73 +2329,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs p) {
     }
 }
 
-// H = xe W1^T where k is short and tiles are many (launch_gemm's rule): 64 x 64
-// tiles, four waves side by side, each a 32 x 32 block over all of k; 32-deep
-// stages in LDS as [k][mn] (rows padded by one float), one in flight in registers.
-// A quarter of a short k is too little to hide gemm_f32_kernel's exchange of partial
-// tiles, and its 74 KB of LDS leave two blocks a CU to cover one another (17 KB
-// here).
-__global__ __launch_bounds__(256) void gemm_f32_short_k_kernel(GemmArgs p) {
-    constexpr int FT = 64, FK = 32, PER = FK * FT / 256;
-    __shared__ float As[FK][FT + 1];
-    __shared__ float Bs[FK][FT + 1];
-    const int e = blockIdx.z;
-    const int ne = expert_rows(p.counts, p.G, p.E, e);
-    const int M = min(ne, p.M), K = p.K, N = p.N;
-    const int m0 = blockIdx.y * FT, n0 = blockIdx.x * FT;
-    if (m0 >= M) return;
-    const float* A = static_cast<const float*>(p.a.base) + e * p.a.estride;
-    const float* B = static_cast<const float*>(p.b.base) + e * p.b.estride;
-    const int lane = threadIdx.x & 63, w = wave_id(), wm = w >> 1, wn = w & 1;
-    const int r = lane & 31, kh = lane >> 5;
-    // thread t: element k = t % 32 of rows t / 32 + 8 u (consecutive threads
-    // read consecutive addresses), zero outside the operand
-    const int kk = threadIdx.x % FK, mr = threadIdx.x / FK;
-    float va[PER], vb[PER];
-    auto load = [&](float (&v)[PER], const float* base, int ld, int r0, int lim, int k0) {
-#pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const int row = r0 + mr + 8 * u;
-            v[u] = row < lim && k0 + kk < K ? base[static_cast<size_t>(row) * ld + k0 + kk] : 0.0f;
-        }
-    };
-    auto put = [&](float (*S)[FT + 1], const float (&v)[PER]) {
-#pragma unroll
-        for (int u = 0; u < PER; ++u) S[kk][mr + 8 * u] = v[u];
-    };
-    f32x16 acc;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-    load(va, A, p.a.ld, m0, M, 0);
-    load(vb, B, p.b.ld, n0, N, 0);
-    for (int k0 = 0; k0 < K; k0 += FK) {
-        put(As, va);
-        put(Bs, vb);
-        lds_barrier();
-        if (k0 + FK < K) {
-            load(va, A, p.a.ld, m0, M, k0 + FK);
-            load(vb, B, p.b.ld, n0, N, k0 + FK);
-        }
-#pragma unroll
-        for (int s = 0; s < FK / 2; ++s)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(As[2 * s + kh][32 * wm + r],
-                                                       Bs[2 * s + kh][32 * wn + r], acc, 0, 0, 0);
-        lds_barrier();
-    }
-    const int n = n0 + 32 * wn + r;
-    if (n >= N) return;
-    const float bias = static_cast<const float*>(p.bias)[e * p.bias_estride + n];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int m = m0 + 32 * wm + 8 * (i / 4) + 4 * kh + (i % 4);
-        if (m >= M) continue;
-        const size_t o = e * p.out_estride + static_cast<size_t>(m) * p.ldo + n;
-        const float v = acc[i] + bias;
-        static_cast<float*>(p.out)[o] = gelu_f(v);
-        static_cast<float*>(p.out2)[o] = gelu_grad_f(v);
-    }
-}
-
 constexpr int kNumCUs = 256;
 
 // One launch over `n` (1 or 2) problems; grid_m_rows[i] bounds problem i's m.
@@ -2506,18 +2442,6 @@ void launch_gemm(const Dims& D, const GemmArgs& a, int grid_m_rows, int sched, h
     // forward 101 -> 111, backward 227 -> 236 at 1576 tokens, d = 384,
     // f = 1536, E = 8)
     const long long big = static_cast<long long>(D.E) * cdiv(grid_m_rows, 64) * cdiv(a.N, 64);
-    // With twelve blocks a CU and k up to 224 the waves of the up-projection stand
-    // side by side instead. Forward, split k / side by side: 1000 rows, E = 64,
-    // d = 64, f = 256 110 / 91 us; 4000 rows, E = 16, d = 192, f = 768 558 / 531;
-    // 4000 rows, E = 16, d = 200, f = 800 667 / 639; below: 6 blocks a CU at
-    // d = 192 even, 1000 rows, E = 16, d = 256, f = 1024 239 / 246, d >= 384 slower.
-    if constexpr (EPI == EPI_FWD1) {
-        if (big >= kNumCUs * 12 && a.K <= 224) {
-            const dim3 grid(cdiv(a.N, 64), cdiv(grid_m_rows, 64), D.E);
-            gemm_f32_short_k_kernel<<<grid, 256, 0, st>>>(a);
-            return;
-        }
-    }
     if (big >= kNumCUs * (EPI == EPI_F32 ? 3 : 12)) {
         const dim3 grid(cdiv(a.N, 64), cdiv(grid_m_rows, 64), D.E);
         gemm_f32_kernel<AK, BK_, EPI, 2><<<grid, 256, 0, st>>>(a);

@@ -83,8 +83,7 @@ F32_CASES = [
     (72, 3080, [512, 500, 449, 0, 64, 65, 480, 1]),
     (3080, 40, [512, 500, 449, 0, 64, 65, 480, 1]),
 ]
-# f32, twelve and more 64 x 64 tiles a CU in the up-projection: k = d up to 224 (waves side by
-# side), and just above
+# f32, twelve and more 64 x 64 tiles a CU in the up-projection: 64 x 64 tiles of a short k
 F32_MANY_TILES = [
     (40, 328, [2049, 0, 1, 63, 64, 65, 2000, 300] * 2),
     (224, 520, [1473, 0, 33, 64, 1408, 127, 128, 129] * 2),
